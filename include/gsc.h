@@ -106,8 +106,9 @@ typedef struct {
                               gsc_stats.res_true (full carry only: the
                               projected carry keeps no x_k to check)          */
     int spmm_kernel;       /* [0 = auto = 1] product kernel layout: 1 one block
-                              row x 64 rhs per wave (the complex64 steps of
-                              GSC_MIXED: 128 rhs per wave, two per lane)      */
+                              row x 64 rhs per workgroup of four waves (the
+                              complex64 steps of GSC_MIXED: 128 rhs, two per
+                              lane)                                           */
     int inner_method;      /* [0 = auto] inner solver for S r' = r: 1 CG (the
                               first solve always runs CG), 2 Chebyshev on the
                               interval of the first CG solve's Ritz values
@@ -153,10 +154,9 @@ typedef struct {
                               80 % of the device memory free at the call.    */
     int row_groups;        /* [0 = auto] workgroup rows of the product and
                               Chebyshev launches (a multiple of 8, at most
-                              65528; capped at one block row per wave); auto:
-                              one block row per wave while a launch stays
-                              within 16384 workgroups, else about 4096
-                              workgroups with equal rows per wave             */
+                              65528; capped at one block row per workgroup);
+                              auto: one block row per workgroup, and about
+                              1024 for the launches that leave partial sums   */
     int reserved[1];
 } gsc_opts;
 

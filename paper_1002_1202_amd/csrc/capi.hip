@@ -410,10 +410,9 @@ gsc_status gsc_spmm(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const double *
         GSC_HIP(hipMemcpyAsync(dseed.get(), iota.data(), Rp * sizeof(int), hipMemcpyHostToDevice, st));
         TileDims td{};
         td.N = N; td.nb = static_cast<int>(p.nb); td.B = p.B; td.Rp = Rp;
-        set_spmm_geometry(td, p);
-        DevBuf<c128> part(static_cast<size_t>(td.Gs) * Rp);
+        set_spmm_geometry(td, false);
         launch_spmm_seed<double>(st, p, td, p.S.get(), p.H.get(), xp.get(), yp.get(), dz.get(), dseed.get(),
-                                 nullptr, part.get());
+                                 nullptr, nullptr);
         c128 *dst = reinterpret_cast<c128 *>(Y);
         if (mem != GSC_MEM_DEVICE) {
             yout.alloc(static_cast<size_t>(N) * nrhs);
@@ -441,9 +440,9 @@ gsc_status gsc_spmm_noalloc(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const 
         const int Rp = (nrhs + 63) / 64 * 64;
         TileDims td{};
         td.N = N; td.nb = static_cast<int>(p.nb); td.B = p.B; td.Rp = Rp;
-        set_spmm_geometry(td, p);
-        // the scratch: shifts [Rp], seed indices [Rp], partial dots [Gs][Rp]
-        // and, unless nrhs is a multiple of 64, padded copies of X and Y
+        set_spmm_geometry(td, false);
+        // the scratch: shifts [Rp], seed indices [Rp] and, unless nrhs is a
+        // multiple of 64, padded copies of X and Y
         const bool direct = Rp == nrhs;
         size_t off = 0;
         auto carve = [&off](size_t bytes) {
@@ -454,7 +453,10 @@ gsc_status gsc_spmm_noalloc(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const 
         const size_t NRp = static_cast<size_t>(N) * Rp;
         const size_t oz = carve(Rp * sizeof(c128));
         const size_t os = carve(Rp * sizeof(int));
-        const size_t op = carve(static_cast<size_t>(td.Gs) * Rp * sizeof(c128));
+        // one complex number per column and group of rows stays free: nothing
+        // uses it here, but the largest call that fits the scratch is part of
+        // the entry point's contract
+        carve(static_cast<size_t>(one_wave_groups(p.nb, Rp / 64)) * Rp * sizeof(c128));
         const size_t ox = direct ? 0 : carve(NRp * sizeof(c128));
         const size_t oy = direct ? 0 : carve(NRp * sizeof(c128));
         if (off > kScratchBytes)
@@ -464,7 +466,6 @@ gsc_status gsc_spmm_noalloc(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const 
         unsigned char *base = static_cast<unsigned char *>(ctx->c.scratch);
         c128 *dz = reinterpret_cast<c128 *>(base + oz);
         int *dseed = reinterpret_cast<int *>(base + os);
-        c128 *part = reinterpret_cast<c128 *>(base + op);
         GSC_HIP(hipMemcpyAsync(dz, alpha_S, static_cast<size_t>(nrhs) * sizeof(c128), hipMemcpyHostToDevice, st));
         k_noalloc_cols<<<div_up(Rp, 256), 256, 0, st>>>(nrhs, Rp, dz, dseed);
         const c128 *xin = reinterpret_cast<const c128 *>(X);
@@ -475,7 +476,7 @@ gsc_status gsc_spmm_noalloc(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const 
             xin = xp;
             yout = reinterpret_cast<c128 *>(base + oy);
         }
-        launch_spmm_seed<double>(st, p, td, p.S.get(), p.H.get(), xin, yout, dz, dseed, nullptr, part);
+        launch_spmm_seed<double>(st, p, td, p.S.get(), p.H.get(), xin, yout, dz, dseed, nullptr, nullptr);
         if (!direct)
             k_pad_cols<<<div_up(static_cast<int64_t>(NRp), 256), 256, 0, st>>>(N, nrhs, Rp, yout,
                                                                                reinterpret_cast<c128 *>(Y), 0);

@@ -1408,11 +1408,12 @@ template <typename T> class TileSolver {
             const bool huge = autob && cb < 128;
             if (huge) cb = 64;
             td.cb = (cb >= 64 && cb < Rp) ? cb : Rp;
-            set_spmm_geometry(td, pr_);
+            set_spmm_geometry(td, kSplit<T> == 1);
             if (req.opts.row_groups > 0) {
-                // caller's row groups, at most one block row per wave
-                const int cap = (td.nb + 3) / 4;
-                td.Gs = (std::min(req.opts.row_groups, cap) + 7) / 8 * 8;
+                // caller's row groups, at most one block row a workgroup (a
+                // wave in the all-complex64 process)
+                const int cap = kSplit<T> == 1 ? (td.nb + 3) / 4 : td.nb;
+                td.Gs = td.Gw = td.G1 = (std::min(req.opts.row_groups, cap) + 7) / 8 * 8;
             }
             td.nt = req.opts.stream_hint == 2 || (req.opts.stream_hint == 0 && huge);
         }
@@ -2084,9 +2085,10 @@ template <typename T> class TileSolver {
         c64 *buf[2] = {mx_ya_.get(), mx_yb_.get()};
         const int cb = td.cb > 0 ? td.cb : td.Rp;
         const double vec = static_cast<double>(last_active_) * td.N;
-        // one complex64 round of K - 1 steps on S y = f (f in mx_f_)
-        auto round = [&](int K, int fin, bool with_dot, const int *skip, int c0, int w, int dot_active_only,
-                         double cols, bool timed) {
+        // one complex64 round of K - 1 steps on S y = f (f in mx_f_); checked:
+        // its last residual is asked for (the last round and the safety round)
+        auto round = [&](int K, int fin, bool with_dot, bool checked, const int *skip, int c0, int w,
+                         int dot_active_only, double cols, bool timed) {
             double rho_prev = 1.0 / sigma, bytes = 0.0;
             if (timed) prof_.begin_group(st_, KP_CHEB_MX);
             for (int kk = 1; kk < K; ++kk) {
@@ -2096,8 +2098,8 @@ template <typename T> class TileSolver {
                 const bool last = kk == K - 1;
                 const int f = last ? fin : 0;
                 launch_cheb_mx(st_, pr_, td, mode, f, last && with_dot, c0, w, S32, buf[kk % 2], mx_f_.get(),
-                               buf[(kk + 1) % 2], Y, t_.r.get(), skip, 1.0 / cheb_theta_, c1, c2, t_.part_d.get(),
-                               dot_part, dot_active_only);
+                               buf[(kk + 1) % 2], Y, t_.r.get(), skip, 1.0 / cheb_theta_, c1, c2,
+                               last && checked ? t_.part_d.get() : nullptr, dot_part, dot_active_only);
                 // algorithmic bytes per column element: gathered y (or f),
                 // f and y_{k-1} streamed, y_{k+1} written; a final step writes
                 // Y (complex128, after reading it for fin 2) and reads r for
@@ -2118,11 +2120,11 @@ template <typename T> class TileSolver {
             for (int j = 0; j < nr; ++j) {
                 if (j > 0) {
                     prof_.begin(st_, KP_MX_RESID, 40.0 * cols * td.N);
-                    launch_mx_resid(st_, pr_, td, c0, w, S64, Y, t_.r.get(), mx_f_.get(), t_.c_done.get(),
-                                    t_.part_d.get());
+                    launch_mx_resid(st_, pr_, td, c0, w, S64, Y, t_.r.get(), mx_f_.get(), t_.c_done.get());
                     prof_.end(st_);
                 }
-                round(mx_plan_[j], j == 0 ? 1 : 2, dot && j == nr - 1, t_.c_done.get(), c0, w, 0, cols, true);
+                round(mx_plan_[j], j == 0 ? 1 : 2, dot && j == nr - 1, j == nr - 1, t_.c_done.get(), c0, w, 0, cols,
+                      true);
             }
         }
         k_cheb_check<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, t_.part_d.get(), inner_tol_ / cheb_rho_, 0, cs);
@@ -2130,9 +2132,8 @@ template <typename T> class TileSolver {
         // (the launches skip every other column; neither timed nor counted)
         for (int c0 = 0; c0 < td.Rp; c0 += cb) {
             const int w = std::min(cb, td.Rp - c0);
-            launch_mx_resid(st_, pr_, td, c0, w, S64, Y, t_.r.get(), mx_f_.get(), t_.c_inner_done.get(),
-                            t_.part_d.get());
-            round(kMxSafetySteps, 2, dot, t_.c_inner_done.get(), c0, w, 1, 0.0, false);
+            launch_mx_resid(st_, pr_, td, c0, w, S64, Y, t_.r.get(), mx_f_.get(), t_.c_inner_done.get());
+            round(kMxSafetySteps, 2, dot, true, t_.c_inner_done.get(), c0, w, 1, 0.0, false);
         }
         k_cheb_check<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, t_.part_d.get(), inner_tol_, 1, cs);
         GSC_HIP(hipGetLastError());
@@ -2171,13 +2172,13 @@ template <typename T> class TileSolver {
         buf[K % 2] = ytarget;
         buf[(K + 1) % 2] = t_.w.get();
         double rho_prev = 1.0 / sigma;
-        auto step = [&](int kk, const int *skip, int c0, int w, int dot_mode) {
+        auto step = [&](int kk, const int *skip, int c0, int w, bool checked, int dot_mode) {
             const double rho = 1.0 / (2.0 * sigma - rho_prev);
             const double c1 = rho * rho_prev, c2 = 2.0 * rho / cheb_delta_;
             const int mode = kk == 1 ? 0 : kk == 2 ? 1 : 2;
             launch_cheb_step<T>(st_, pr_, td, mode, c0, w, Sv, buf[kk % 2], t_.r.get(), buf[(kk + 1) % 2],
-                                    skip, 1.0 / cheb_theta_, c1, c2, t_.part_d.get(), dot ? dot_part : nullptr,
-                                    dot ? dot_mode : 0);
+                                skip, 1.0 / cheb_theta_, c1, c2, checked ? t_.part_d.get() : nullptr,
+                                dot ? dot_part : nullptr, dot ? dot_mode : 0);
             rho_prev = rho;
         };
         // the K - 1 steps of each column block run back to back (columns are
@@ -2191,15 +2192,15 @@ template <typename T> class TileSolver {
         for (int c0 = 0; c0 < td.Rp; c0 += cb) {
             rho_prev = 1.0 / sigma;
             for (int k = 1; k < K; ++k, ++launches)
-                step(k, t_.c_done.get(), c0, std::min(cb, td.Rp - c0), k == K - 1 ? 1 : 0);
+                step(k, t_.c_done.get(), c0, std::min(cb, td.Rp - c0), k == K - 1, k == K - 1 ? 1 : 0);
         }
         prof_.end_group(st_, launches, bytes);
         k_cheb_check<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, t_.part_d.get(), inner_tol_ / cheb_rho_, 0, cs);
         // extra steps for the columns that failed the check (bytes counted
         // from the check's outcome are not known here: counted as zero)
         prof_.begin_group(st_, KP_CHEB);
-        step(K, t_.c_inner_done.get(), 0, td.Rp, 0);
-        step(K + 1, t_.c_inner_done.get(), 0, td.Rp, 2);
+        step(K, t_.c_inner_done.get(), 0, td.Rp, false, 0);
+        step(K + 1, t_.c_inner_done.get(), 0, td.Rp, true, 2);
         prof_.end_group(st_, 2, 0.0);
         k_cheb_check<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, t_.part_d.get(), inner_tol_, 1, cs);
         GSC_HIP(hipGetLastError());
