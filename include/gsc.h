@@ -86,7 +86,9 @@ typedef struct {
                               Chebyshev rounds (FP32 S and arithmetic) refined
                               by FP64 residuals to the same inner tolerance,
                               so results keep the FP64 accuracy (needs the
-                              Chebyshev inner solve; with CG it is FP64).
+                              Chebyshev inner solve; with CG it is FP64, and
+                              so it is for systems of a few hundred orbitals,
+                              whose columns run in one workgroup each).
                               GSC_C64: complex64 vectors and products for the
                               whole seed process, FP64 scalars and dots; its
                               accuracy is limited to about cond(z S - H) times
@@ -164,7 +166,9 @@ typedef struct {
  * nshift*nrhs entries laid out [k][r] (any of them may be NULL). */
 typedef struct {
     int outer_iters;              /* largest outer iteration count of a tile  */
-    long long inner_iters;        /* inner CG steps summed over tiles          */
+    long long inner_iters;        /* inner CG steps summed over tiles (one
+                                     workgroup per column: the Chebyshev steps
+                                     of its longest column)                   */
     int switches;                 /* seed switches summed over rhs            */
     int restarts;                 /* collinear restarts summed over rhs       */
     long long shift_rhs_iters;    /* sum over iterations and rhs of the
@@ -444,7 +448,8 @@ gsc_status gsc_band_energy_vjp(gsc_ctx *ctx, const gsc_pair *pair, int nshift, c
  * "lz_scale"), the summed
  * device milliseconds, the number of launches and the summed algorithmic
  * bytes those launches must move (the method's own reads and writes, no re-reads).  GSC_E_ARG for an
- * unknown name. */
+ * unknown name.  While timing is on, systems of a few hundred orbitals run
+ * these kernels too instead of one workgroup per column. */
 gsc_status gsc_profile_enable(gsc_ctx *ctx, int on);
 /* Restrict the event timing to one kernel name (NULL: time every kernel);
  * byte counting continues for all kernels.  Event pairs cost a few

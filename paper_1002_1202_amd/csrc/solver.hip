@@ -22,6 +22,7 @@
 #include <cmath>
 #include <cstring>
 
+#include "small.h"
 #include "solver.h"
 #include "spmm.h"
 
@@ -548,6 +549,8 @@ __global__ void k_to_c64(size_t n, const c128 *a, c64 *b) {
     const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) b[i] = ccast<float>(a[i]);
 }
+
+__global__ void k_zero_int(int *v) { *v = 0; }
 
 __global__ void k_status(int Rp, ColState cs, Status *st) {
     __shared__ int a[kBlock], b[kBlock], s[kBlock], f[kBlock];
@@ -1585,6 +1588,7 @@ template <typename T> class TileSolver {
 
     int run(const gsc_opts &o, double inner_tol, int seed0) {
         init_phase(o, inner_tol, seed0);
+        if (small_ok(o)) return run_small(o);
         auto &td = t_.td;
         ColState cs = t_.cols();
         ShiftState ss = t_.shifts(dz_);
@@ -1662,6 +1666,51 @@ template <typename T> class TileSolver {
         return n;
     }
 
+
+    // Whether one workgroup per column runs the iteration (small.hip): FP64
+    // vectors, the Chebyshev inner solve at a fixed tolerance (the relaxed one
+    // follows all columns), no per-kernel timing (there is one kernel).
+    bool small_ok(const gsc_opts &o) const {
+        return std::is_same<T, double>::value && cheb_ok_ && !o.inner_relax && !prof_.on &&
+               small_fits(pr_, t_.Mu + t_.srow, t_.td.R, ctx_.num_cu);
+    }
+    int run_small(const gsc_opts &o) {
+        auto &td = t_.td;
+        if constexpr (std::is_same<T, double>::value) {
+            DevBuf<int> sw(1);
+            k_zero_int<<<1, 1, 0, st_>>>(sw.get());
+            SmallSolve a{};
+            a.nj = small_lane_blocks(pr_);
+            DevBuf<double> packed(small_packed(pr_, a.nj));
+            a.packed = packed.get();
+            a.rowptr = pr_.rowptr.get(); a.colidx = pr_.colidx.get(); a.S = pr_.S.get(); a.H = pr_.H.get();
+            a.N = td.N; a.nb = td.nb; a.B = td.B; a.K = td.K; a.R = td.R; a.Rp = td.Rp; a.m = td.m;
+            a.p = t_.p.get(); a.r = t_.r.get(); a.rp = t_.ring.get();
+            a.cs = t_.cols(); a.ss = t_.shifts(dz_);
+            a.theta = cheb_theta_; a.delta = cheb_delta_; a.rho = cheb_rho_; a.inner_tol = inner_tol_;
+            a.steps = cheb_steps_;
+            a.tol = o.tol; a.max_iter = o.max_iter;
+            if (full_) {
+                a.X = t_.X; a.P = t_.P.get(); a.ringT = t_.ringT.get(); a.ldx = ldk_x_; a.ldp = t_.ldk;
+            } else {
+                a.Mu = t_.Mu; a.srow = t_.srow; a.rhs = drhs_; a.pidx = t_.pidx.get();
+                a.h = t_.h.get(); a.g = t_.gacc.get(); a.dh = t_.dh.get(); a.wE = req_.wE;
+                if (req_.vjp) a.acc = req_.vjp_acc + static_cast<size_t>(r0_) * (t_.Mu + t_.srow) * 3;
+            }
+            a.switches = sw.get();
+            launch_small_solve(st_, pr_, a);
+            std::vector<int> it(td.Rp);
+            int nsw = 0;
+            GSC_HIP(hipMemcpyAsync(it.data(), t_.c_iters.get(), it.size() * sizeof(int), hipMemcpyDeviceToHost, st_));
+            GSC_HIP(hipMemcpyAsync(&nsw, sw.get(), sizeof(int), hipMemcpyDeviceToHost, st_));
+            check_status(false);
+            const int n = *std::max_element(it.begin(), it.end());
+            switches_ += nsw;
+            inner_total_ += static_cast<long long>(n) * (cheb_steps_ - 1);
+            return n;
+        }
+        return 0;
+    }
 
     // Generalised Lanczos (Sec. 3.2) for the P processes of this tile (two per
     // column).  Device outputs: a, b [2Rp][mmax] (zeroed here; b[p][0] = 0),
