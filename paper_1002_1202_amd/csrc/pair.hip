@@ -48,11 +48,12 @@ void validate_and_upload(Pair &p, int block, int64_t nbrows, const int64_t *rowp
     for (int64_t i = 0; i <= nbrows; ++i) rp32[i] = static_cast<int32_t>(rowptr[i]);
     hipStream_t st = p.ctx->stream;
     p.rowptr.alloc(nbrows + 1);
-    p.colidx.alloc(nnzb);
+    p.colidx.alloc(nnzb + 1);    // the products read one index ahead
     p.brow.alloc(nnzb);
     p.mirror.alloc(nnzb);
     GSC_HIP(hipMemcpyAsync(p.rowptr.get(), rp32.data(), rp32.size() * 4, hipMemcpyHostToDevice, st));
     GSC_HIP(hipMemcpyAsync(p.colidx.get(), colidx, nnzb * 4, hipMemcpyHostToDevice, st));
+    GSC_HIP(hipMemcpyAsync(p.colidx.get() + nnzb, colidx, 4, hipMemcpyHostToDevice, st));
     GSC_HIP(hipMemcpyAsync(p.brow.get(), brow.data(), nnzb * 4, hipMemcpyHostToDevice, st));
     GSC_HIP(hipMemcpyAsync(p.mirror.get(), mirror.data(), nnzb * 4, hipMemcpyHostToDevice, st));
     const size_t nv = static_cast<size_t>(nnzb) * block * block;

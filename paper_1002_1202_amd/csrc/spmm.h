@@ -61,24 +61,47 @@ template <typename V, int B> __device__ inline void mac_block(V (&acc)[B], const
 }
 
 // acc += M x over the n stored blocks from s0 on (TWO: acc2 += M2 x as well).
-// The loop stays as it is, U blocks at a time: what other waves there are hides
-// its latencies better than registers spent on loads in flight (one block ahead
-// or two at a time, against none: 256 H2O x 1536 columns 60.6 and 49.2 against
-// 47.4 us a step, 3,000 H2O x 96 mixed 32.6 and 29.5 against 28.4).
-template <typename V, int B, int U, bool TWO>
+// What other waves there are hides the loop's latencies better than registers
+// spent on loads in flight (x of one block ahead or two blocks at a time, against
+// none: 256 H2O x 1536 columns 60.6 and 49.2 against 47.4 us a step, 3,000 H2O x
+// 96 mixed 32.6 and 29.5 against 28.4).  The index of the next block is the
+// exception (AHEAD): scalar loads end together, so an index waits for M's values
+// of its block, and the x loads for both (whole solves without and with it: 256
+// H2O x 1536 360 -> 340 ms, 3,000 H2O x 96 mixed 892 -> 847, 4,096 Si x 256 745 ->
+// 741).  It reads one index past the row, which the pattern's array has room for.
+template <typename V, int B, bool AHEAD, bool TWO>
 __device__ inline void row_blocks(V (&acc)[B], V (&acc2)[B], int s0, int n, const int32_t *colidx,
                                   const scalar_t<V> *M, const scalar_t<V> *M2, const V *base, size_t ld, int lane) {
     const_mem<int32_t> ci = as_const(colidx + s0);
     const_mem<scalar_t<V>> m = as_const(M + static_cast<size_t>(s0) * B * B);
     const_mem<scalar_t<V>> m2 = as_const(M2 + static_cast<size_t>(s0) * B * B);
-#pragma unroll U
-    for (int j = 0; j < n; ++j) {
+    auto block = [&](int J) {
         V x[B];
-        load_block<V, B>(x, base, ci[j], ld, lane);
-        mac_block<V, B>(acc, m, x);
-        if constexpr (TWO) mac_block<V, B>(acc2, m2, x);
-        m += B * B;
-        if constexpr (TWO) m2 += B * B;
+        load_block<V, B>(x, base, J, ld, lane);
+        return [=](V(&a1)[B], V(&a2)[B]) {
+            mac_block<V, B>(a1, m, x);
+            if constexpr (TWO) mac_block<V, B>(a2, m2, x);
+        };
+    };
+    if constexpr (AHEAD) {
+        int J = ci[0];
+#pragma unroll 1
+        for (int j = 0; j < n; ++j) {
+            const auto add = block(J);
+            int Jn = ci[j + 1];
+            add(acc, acc2);
+            m += B * B;
+            if constexpr (TWO) m2 += B * B;
+            asm("" : "+s"(Jn));       // keeps its load up there
+            J = Jn;
+        }
+    } else {
+#pragma unroll(B == 4 ? 2 : 1)
+        for (int j = 0; j < n; ++j) {
+            block(ci[j])(acc, acc2);
+            m += B * B;
+            if constexpr (TWO) m2 += B * B;
+        }
     }
 }
 
@@ -132,8 +155,7 @@ __device__ inline void walk_rows(bool act, int nb, int g, int w, int lane, const
                 for (int o = 0; o < kOwn; ++o)
                     if (B % SPLIT == 0 || q + o * SPLIT < B) ex[o] = load(row + q + o * SPLIT);
             }
-            row_blocks<V, B, SPLIT == 1 && B == 4 ? 2 : 1, TWO>(acc, acc2, b0 + lo, hi - lo, colidx, M, M2, base, ld,
-                                                                lane);
+            row_blocks<V, B, (SPLIT > 1), TWO>(acc, acc2, b0 + lo, hi - lo, colidx, M, M2, base, ld, lane);
             combine(acc, acc2);
             if constexpr (SPLIT == 1) {
 #pragma unroll
