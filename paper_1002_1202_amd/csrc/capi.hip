@@ -139,18 +139,15 @@ __global__ void k_vjp_assemble(int R, int M, const c128 *acc, const int64_t *vid
     dS[v] += grad_E * (-f) * (A[0].im + A[2].im);
 }
 
-__global__ void k_pad_cols(int N, int R, int Rp, const c128 *in, c128 *out, int to_padded) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= static_cast<int64_t>(N) * Rp) return;
-    const int64_t i = t / Rp;
-    const int c = static_cast<int>(t % Rp);
-    if (to_padded) out[t] = c < R ? in[i * R + c] : c128{0, 0};
-    else if (c < R) out[i * R + c] = in[t];
+// whether two arrays of `bytes` share memory
+bool overlap(const void *a, const void *b, size_t bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + bytes && y < x + bytes;
 }
 
 // ------------------------------------------------------------------ allocation-free product
-// gsc_spmm_noalloc works in this fixed array instead of allocating: one copy
-// per device, part of the code object, held until the process ends.  In host
+// gsc_spmm_noalloc keeps what it copies (X, when Y overlaps it) in this fixed
+// array instead of allocating: one copy per device, part of the code object, held until the process ends.  In host
 // code the name is only a host-side stand-in, never a device address: host
 // code uses the address hipGetSymbolAddress returns, fetched once per device
 // (with that device current) when a context is created, and kept in the
@@ -172,14 +169,6 @@ void *scratch_address(int device) {
         addr[device] = ptr;
     }
     return addr[device];
-}
-
-// per-column shift index c and zero shifts for the padding columns c >= R
-__global__ void k_noalloc_cols(int R, int Rp, c128 *z, int *seed) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= Rp) return;
-    seed[c] = c;
-    if (c >= R) z[c] = c128{0.0, 0.0};
 }
 
 // (S G_k)_aa for the unit right-hand sides e_a, a = orb_idx[r], into the
@@ -390,37 +379,23 @@ gsc_status gsc_spmm(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const double *
         const Pair &p = pair->p;
         hipStream_t st = ctx->c.stream;
         const int N = static_cast<int>(p.n);
-        const int Rp = (nrhs + 63) / 64 * 64;
-        DevBuf<c128> xin, xp(static_cast<size_t>(N) * Rp), yp(static_cast<size_t>(N) * Rp), yout;
+        const size_t n = static_cast<size_t>(N) * nrhs;
+        DevBuf<c128> xin, yout;
         const c128 *src = reinterpret_cast<const c128 *>(X);
-        if (mem != GSC_MEM_DEVICE) {
-            xin.alloc(static_cast<size_t>(N) * nrhs);
-            GSC_HIP(hipMemcpyAsync(xin.get(), X, xin.n * sizeof(c128), hipMemcpyHostToDevice, st));
+        c128 *dst = reinterpret_cast<c128 *>(Y);
+        const bool host = mem != GSC_MEM_DEVICE;
+        if (host || overlap(X, Y, n * sizeof(c128))) {
+            xin.alloc(n);
+            GSC_HIP(hipMemcpyAsync(xin.get(), X, n * sizeof(c128),
+                                   host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st));
             src = xin.get();
         }
-        const int64_t tot = static_cast<int64_t>(N) * Rp;
-        k_pad_cols<<<div_up(tot, 256), 256, 0, st>>>(N, nrhs, Rp, src, xp.get(), 1);
-        std::vector<c128> za(Rp, c128{0, 0});
-        std::vector<int> iota(Rp);
-        for (int c = 0; c < Rp; ++c) iota[c] = c;
-        for (int c = 0; c < nrhs; ++c) za[c] = c128{alpha_S[2 * c], alpha_S[2 * c + 1]};
-        DevBuf<c128> dz(Rp);
-        DevBuf<int> dseed(Rp);
-        GSC_HIP(hipMemcpyAsync(dz.get(), za.data(), Rp * sizeof(c128), hipMemcpyHostToDevice, st));
-        GSC_HIP(hipMemcpyAsync(dseed.get(), iota.data(), Rp * sizeof(int), hipMemcpyHostToDevice, st));
-        TileDims td{};
-        td.N = N; td.nb = static_cast<int>(p.nb); td.B = p.B; td.Rp = Rp;
-        set_spmm_geometry(td, false);
-        launch_spmm_seed<double>(st, p, td, p.S.get(), p.H.get(), xp.get(), yp.get(), dz.get(), dseed.get(),
-                                 nullptr, nullptr);
-        c128 *dst = reinterpret_cast<c128 *>(Y);
-        if (mem != GSC_MEM_DEVICE) {
-            yout.alloc(static_cast<size_t>(N) * nrhs);
+        if (host) {
+            yout.alloc(n);
             dst = yout.get();
         }
-        k_pad_cols<<<div_up(tot, 256), 256, 0, st>>>(N, nrhs, Rp, yp.get(), dst, 0);
-        GSC_HIP(hipGetLastError());
-        if (mem != GSC_MEM_DEVICE)
+        launch_product(st, p, nrhs, alpha_S, src, dst);
+        if (host)
             GSC_HIP(hipMemcpyAsync(Y, yout.get(), yout.n * sizeof(c128), hipMemcpyDeviceToHost, st));
         GSC_HIP(hipStreamSynchronize(st));
         return GSC_OK;
@@ -438,49 +413,35 @@ gsc_status gsc_spmm_noalloc(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const 
         hipStream_t st = ctx->c.stream;
         const int N = static_cast<int>(p.n);
         const int Rp = (nrhs + 63) / 64 * 64;
-        TileDims td{};
-        td.N = N; td.nb = static_cast<int>(p.nb); td.B = p.B; td.Rp = Rp;
-        set_spmm_geometry(td, false);
-        // the scratch: shifts [Rp], seed indices [Rp] and, unless nrhs is a
-        // multiple of 64, padded copies of X and Y
-        const bool direct = Rp == nrhs;
-        size_t off = 0;
-        auto carve = [&off](size_t bytes) {
-            const size_t o = off;
-            off += (bytes + 255) / 256 * 256;
+        // The largest call that is accepted is part of the entry point's
+        // contract: one that leaves room for padded copies of X and Y (nrhs no
+        // multiple of 64), the shifts, the seed indices and a complex number per
+        // column and group of rows.
+        const bool ragged = Rp != nrhs;
+        size_t need = 0;
+        auto carve = [&need](size_t bytes) {
+            const size_t o = need;
+            need += (bytes + 255) / 256 * 256;
             return o;
         };
         const size_t NRp = static_cast<size_t>(N) * Rp;
-        const size_t oz = carve(Rp * sizeof(c128));
-        const size_t os = carve(Rp * sizeof(int));
-        // one complex number per column and group of rows stays free: nothing
-        // uses it here, but the largest call that fits the scratch is part of
-        // the entry point's contract
+        carve(Rp * sizeof(c128));
+        carve(Rp * sizeof(int));
         carve(static_cast<size_t>(one_wave_groups(p.nb, Rp / 64)) * Rp * sizeof(c128));
-        const size_t ox = direct ? 0 : carve(NRp * sizeof(c128));
-        const size_t oy = direct ? 0 : carve(NRp * sizeof(c128));
-        if (off > kScratchBytes)
-            throw Error(GSC_E_ARG, "gsc_spmm_noalloc needs " + std::to_string(off) +
+        const size_t ox = ragged ? carve(NRp * sizeof(c128)) : 0;
+        if (ragged) carve(NRp * sizeof(c128));
+        if (need > kScratchBytes)
+            throw Error(GSC_E_ARG, "gsc_spmm_noalloc needs " + std::to_string(need) +
                                        " bytes of scratch, more than its maximum of " +
                                        std::to_string(kScratchBytes) + " (fewer rhs or a multiple of 64)");
-        unsigned char *base = static_cast<unsigned char *>(ctx->c.scratch);
-        c128 *dz = reinterpret_cast<c128 *>(base + oz);
-        int *dseed = reinterpret_cast<int *>(base + os);
-        GSC_HIP(hipMemcpyAsync(dz, alpha_S, static_cast<size_t>(nrhs) * sizeof(c128), hipMemcpyHostToDevice, st));
-        k_noalloc_cols<<<div_up(Rp, 256), 256, 0, st>>>(nrhs, Rp, dz, dseed);
-        const c128 *xin = reinterpret_cast<const c128 *>(X);
-        c128 *yout = reinterpret_cast<c128 *>(Y);
-        if (!direct) {
-            c128 *xp = reinterpret_cast<c128 *>(base + ox);
-            k_pad_cols<<<div_up(static_cast<int64_t>(NRp), 256), 256, 0, st>>>(N, nrhs, Rp, xin, xp, 1);
-            xin = xp;
-            yout = reinterpret_cast<c128 *>(base + oy);
+        const c128 *src = reinterpret_cast<const c128 *>(X);
+        const size_t n = static_cast<size_t>(N) * nrhs;
+        if (ragged && overlap(X, Y, n * sizeof(c128))) {
+            c128 *xs = reinterpret_cast<c128 *>(static_cast<unsigned char *>(ctx->c.scratch) + ox);
+            GSC_HIP(hipMemcpyAsync(xs, X, n * sizeof(c128), hipMemcpyDeviceToDevice, st));
+            src = xs;
         }
-        launch_spmm_seed<double>(st, p, td, p.S.get(), p.H.get(), xin, yout, dz, dseed, nullptr, nullptr);
-        if (!direct)
-            k_pad_cols<<<div_up(static_cast<int64_t>(NRp), 256), 256, 0, st>>>(N, nrhs, Rp, yout,
-                                                                               reinterpret_cast<c128 *>(Y), 0);
-        GSC_HIP(hipGetLastError());
+        launch_product(st, p, nrhs, alpha_S, src, reinterpret_cast<c128 *>(Y));
         GSC_HIP(hipStreamSynchronize(st));
         return GSC_OK;
     });

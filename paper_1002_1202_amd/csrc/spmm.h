@@ -198,7 +198,11 @@ template <typename T> inline int seed_split(int nb, int chunks) {
     return kSplit<T> == 1 || static_cast<int64_t>(nb) * chunks >= 8192 ? 1 : kSplit<T>;
 }
 
-// partial == nullptr: the product alone, no dots
+// Y = factor_c S X - H X, X and Y [N][R] of the caller (not overlapping),
+// factors [R] complex in host memory
+void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors, const c128 *X, c128 *Y);
+
+// with the dots' partials
 template <typename T>
 void launch_spmm_seed(hipStream_t st, const Pair &pr, const TileDims &td, const T *Sv, const T *Hv,
                       const cpx<T> *p, cpx<T> *q, const c128 *z, const int *seed, const int *skip,

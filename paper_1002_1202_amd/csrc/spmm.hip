@@ -7,6 +7,7 @@
 // stored value the product does 2 (S only) or 4 (S and H) FMAs per complex
 // column against >= 16 bytes of vector traffic, far below the FP64 ridge.
 #include <algorithm>
+#include <cstring>
 
 #include "spmm.h"
 
@@ -29,10 +30,10 @@ __device__ inline void wave_sums_store(P v, P (*red)[64], int w, int lane, P *ou
 
 }  // namespace
 
-// q = zs_c * (S p) - H p for every active column c; DOT: also the per-column
+// q = zs_c * (S p) - H p for every active column c and the per-column
 // unconjugated partial dot  sum_i p_i q_i  (the denominator of alpha,
 // eq. CGp:r with the S-bilinear form) of this row group.
-template <typename T, int B, int SPLIT, bool DOT>
+template <typename T, int B, int SPLIT>
 __global__ __launch_bounds__(kBlock) void k_spmm_seed(
     int nb, int Rp, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ Sv, const T *__restrict__ Hv, const cpx<T> *__restrict__ p,
@@ -48,24 +49,83 @@ __global__ __launch_bounds__(kBlock) void k_spmm_seed(
     const size_t ld = Rp;
     const V *pc = p + cx * 64;
     V *qc = q + cx * 64;
-    const bool act = skip == nullptr || !skip[col];
+    const bool act = !skip[col];
     const c128 zs = act ? z[seed[col]] : c128{0, 0};
     const V zt = ccast<T>(zs);
     c128 dot{0.0, 0.0};
     walk_rows<SPLIT, true, false>(
         act, nb, g, w, lane, rowptr, colidx, Sv, Hv, pc, ld, red, red,
-        [&](size_t row) { return DOT ? (pc + row * ld)[lane] : V{}; },
+        [&](size_t row) { return (pc + row * ld)[lane]; },
         [&](V(&aS)[B], V(&aH)[B]) {
 #pragma unroll
             for (int a = 0; a < B; ++a) aS[a] = zt * aS[a] - aH[a];
         },
         [&](size_t row, V v, V, V own) {
             (qc + row * ld)[lane] = v;
-            if constexpr (DOT) dot = dot + ccast<double>(own) * ccast<double>(v);
+            dot = dot + ccast<double>(own) * ccast<double>(v);
         });
-    if constexpr (DOT) {
-        __shared__ c128 redd[kWavesPerBlock][64];
-        wave_sums_store(dot, redd, w, lane, partial + static_cast<size_t>(g) * Rp + col);
+    __shared__ c128 redd[kWavesPerBlock][64];
+    wave_sums_store(dot, redd, w, lane, partial + static_cast<size_t>(g) * Rp + col);
+}
+
+// The same product for a caller's own X and Y, R columns wide: rows of any
+// length, the lanes beyond the last column masked, and the columns' factors in
+// the kernel's arguments.  Against padded copies of X and Y around the kernel
+// above and factors copied to the device: 64 Si x 8 columns 36.4 -> 24 us a call,
+// 8,192 Si x 250 278 -> 183 us.  Four waves share a row at every size (one wave a
+// row: 102 against 85 us for 8,192 Si x 128); without the dots there is nothing to
+// load beside the product.
+constexpr int kFactors = 128;
+struct Factors { c128 z[kFactors]; };
+template <int B>
+__global__ __launch_bounds__(kBlock) void k_product(int nb, int R, int ncols, const int32_t *__restrict__ rowptr,
+                                                    const int32_t *__restrict__ colidx,
+                                                    const double *__restrict__ Sv, const double *__restrict__ Hv,
+                                                    const c128 *__restrict__ X, c128 *__restrict__ Y, int same,
+                                                    Factors f) {
+    constexpr int SPLIT = kSplit<double>;
+    __shared__ RowSums<c128, B, SPLIT> red;
+    int cx, g;
+    xcd_remap_chunks(cx, g);
+    const int lane = threadIdx.x & 63;
+    const int w = wave_id();
+    const int col = cx * 64 + lane;
+    const c128 *x = X + cx * 64;
+    c128 *y = Y + cx * 64;
+    const size_t ld = R;
+    const bool act = col < ncols;
+    const c128 z = f.z[same || !act ? 0 : col];
+    struct None {};
+    walk_rows<SPLIT, true, false>(
+        act, nb, g, w, lane, rowptr, colidx, Sv, Hv, x, ld, red, red, [](size_t) { return None{}; },
+        [&](c128(&aS)[B], c128(&aH)[B]) {
+#pragma unroll
+            for (int a = 0; a < B; ++a) aS[a] = z * aS[a] - aH[a];
+        },
+        [&](size_t row, c128 v, c128, None) { (y + row * ld)[lane] = v; });
+}
+
+void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors, const c128 *X, c128 *Y) {
+    const c128 *z = reinterpret_cast<const c128 *>(factors);
+    bool same = true;
+    for (int c = 1; c < R && same; ++c) same = std::memcmp(z, z + c, sizeof(c128)) == 0;
+    for (int c0 = 0; c0 < R;) {
+        const int n = same ? R : std::min(R - c0, kFactors);
+        Factors f{};
+        std::memcpy(f.z, z + c0, (same ? 1 : n) * sizeof(c128));
+        TileDims td{};
+        td.nb = static_cast<int>(pr.nb);
+        td.Rp = (n + 63) / 64 * 64;
+        set_spmm_geometry(td, false);
+        const dim3 grid(td.Rp / 64, td.Gw);
+#define GSC_PRODUCT(BB)                                                                                           \
+    k_product<BB><<<grid, kBlock, 0, st>>>(td.nb, R, n, pr.rowptr.get(), pr.colidx.get(), pr.S.get(), pr.H.get(), \
+                                           X + c0, Y + c0, same, f)
+        if (pr.B == 4) GSC_PRODUCT(4);
+        else GSC_PRODUCT(6);
+#undef GSC_PRODUCT
+        GSC_HIP(hipGetLastError());
+        c0 += n;
     }
 }
 
@@ -416,14 +476,13 @@ void launch_spmm_seed(hipStream_t st, const Pair &pr, const TileDims &td, const 
                       const cpx<T> *p, cpx<T> *q, const c128 *z, const int *seed, const int *skip,
                       c128 *partial) {
     const int split = seed_split<T>(td.nb, td.Rp / 64);
-    dim3 grid(td.Rp / 64, partial ? td.Gs : split == 1 ? td.G1 : td.Gw), block(kBlock);
-#define GSC_SEED(BB, SP, D)                                                                                         \
-    k_spmm_seed<T, BB, SP, D><<<grid, block, 0, st>>>(td.nb, td.Rp, pr.rowptr.get(), pr.colidx.get(), Sv, Hv, p, q, \
-                                                      z, seed, skip, partial)
-#define GSC_SEED_S(BB, D) \
-    if (split == 1) GSC_SEED(BB, 1, D); else GSC_SEED(BB, kSplit<T>, D);
-    if (pr.B == 4) { if (partial) { GSC_SEED_S(4, true) } else { GSC_SEED_S(4, false) } }
-    else { if (partial) { GSC_SEED_S(6, true) } else { GSC_SEED_S(6, false) } }
+    dim3 grid(td.Rp / 64, td.Gs), block(kBlock);
+#define GSC_SEED(BB, SP)                                                                                         \
+    k_spmm_seed<T, BB, SP><<<grid, block, 0, st>>>(td.nb, td.Rp, pr.rowptr.get(), pr.colidx.get(), Sv, Hv, p, q, \
+                                                   z, seed, skip, partial)
+#define GSC_SEED_S(BB) \
+    if (split == 1) GSC_SEED(BB, 1); else GSC_SEED(BB, kSplit<T>);
+    if (pr.B == 4) { GSC_SEED_S(4) } else { GSC_SEED_S(6) }
 #undef GSC_SEED_S
 #undef GSC_SEED
     GSC_HIP(hipGetLastError());
