@@ -191,7 +191,7 @@ __device__ inline void flush_column(const SmallSolve &s, int c, int n0, int n1, 
         for (int j = 0; j < kFlushSteps; ++j)
             rr[j] = j < cnt ? s.ringT[((t0 + j) % s.m) * NR + base] : c128{0, 0};
         for (int k = grp; k < s.K; k += groups) {
-            const int last = s.ss.last[static_cast<size_t>(k) * s.Rp + c];
+            const int last = s.ss.last[shift_at(s.K, k, c)];
             const int kc = min(cnt, last >= n1 ? cnt : last + 1 - t0);
             if (kc <= 0) continue;
             const size_t ox = static_cast<size_t>(k) * s.ldx + base, op = static_cast<size_t>(k) * s.ldp + base;
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
         const c128 tail = uni(cdiv(alpha * beta_prev, alpha_prev));
         int cnt = 0;
         for (int k = tk; k < K; k += nt) {
-            const size_t idx = static_cast<size_t>(k) * Rp + c;
+            const size_t idx = shift_at(K, k, c);
             if (s.ss.last[idx] != kFrozenNever) continue;
             ++cnt;
             const c128 pi = s.ss.pi[idx], pim = s.ss.pi_prev[idx];
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
             if (s.dh == nullptr) {
                 for (int t = tk; t < K * M; t += nt) {
                     const int k = t / M, mm = t % M;
-                    const size_t idx = static_cast<size_t>(k) * Rp + c;
+                    const size_t idx = shift_at(K, k, c);
                     if (s.ss.last[idx] != kFrozenNever) continue;
                     const size_t f = coef_at(s.ss, k, c, slot), o = idx * M + mm;
                     const c128 hv = s.ss.ra[f] * cr[mm] + s.ss.rb[f] * s.h[o];
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
                 if (vset < sets) {
                     const c128 crm = cr[vm];
                     for (int k = here(vset); k < K; k += sets) {
-                        const size_t idx = static_cast<size_t>(k) * Rp + c;
+                        const size_t idx = shift_at(K, k, c);
                         if (s.ss.last[idx] != kFrozenNever) continue;
                         const size_t f = coef_at(s.ss, k, c, slot), o = idx * M + vm;
                         const c128 hold = s.h[o], dhold = s.dh[o];
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
         double best = -1.0;
         int bestk = 0x7fffffff, left = 0;
         for (int k = tk; k < K; k += nt) {
-            const size_t idx = static_cast<size_t>(k) * Rp + c;
+            const size_t idx = shift_at(K, k, c);
             if (s.ss.last[idx] != kFrozenNever) continue;
             const c128 pin = s.ss.pi_next[idx];
             s.ss.pi_prev[idx] = s.ss.pi[idx];
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
         } else if (cabs(rho_new) == 0.0) {
             flags |= FLAG_BREAKDOWN;
             break;
-        } else if (s.ss.last[static_cast<size_t>(seed) * Rp + c] != kFrozenNever) {
+        } else if (s.ss.last[shift_at(K, seed, c)] != kFrozenNever) {
             sw = s.X != nullptr ? 1 : 2;
         }
         alpha_prev = alpha;
@@ -506,7 +506,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
         if (done) break;
         if (sw != 0) {
             ++switches;
-            const size_t ix = static_cast<size_t>(bestk) * Rp + c;
+            const size_t ix = shift_at(K, bestk, c);
             const c128 cc = uni(s.ss.pi[ix]), ccm = uni(s.ss.pi_prev[ix]);
             __syncthreads();         // read before the rescale; P of the flush is visible
             if (sw == 1) {
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
                 alpha_prev = uni(alpha * qq);
                 swc = uni(cdiv(c128{1.0, 0.0}, cc));
                 for (int k = tk; k < K; k += nt) {
-                    const size_t idx = static_cast<size_t>(k) * Rp + c;
+                    const size_t idx = shift_at(K, k, c);
                     s.ss.pi[idx] = cdiv(s.ss.pi[idx], cc);
                     s.ss.pi_prev[idx] = cdiv(s.ss.pi_prev[idx], ccm);
                 }
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
                 alpha_prev = {1.0, 0.0};
                 beta_prev = {0.0, 0.0};
                 for (int k = tk; k < K; k += nt) {
-                    const size_t idx = static_cast<size_t>(k) * Rp + c;
+                    const size_t idx = shift_at(K, k, c);
                     if (s.ss.last[idx] == kFrozenNever) {
                         const c128 pik = s.ss.pi[idx];
                         if (s.ss.dpi != nullptr)
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(MAXT) void k_small_solve(SmallSolve s) {
                     }
                 }
                 for (int t = tk; t < K * M; t += nt) {
-                    const size_t o = (static_cast<size_t>(t / M) * Rp + c) * M + t % M;
+                    const size_t o = shift_at(K, t / M, c) * M + t % M;
                     s.h[o] = {0, 0};
                     if (s.dh != nullptr) s.dh[o] = {0, 0};
                 }

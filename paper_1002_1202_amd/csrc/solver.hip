@@ -97,7 +97,7 @@ __global__ void k_init_cols(int R, int Rp, int seed0, ColState cs) {
 __global__ void k_init_shifts(int K, int R, int Rp, ShiftState ss) {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t >= static_cast<int64_t>(K) * Rp) return;
-    const int c = static_cast<int>(t % Rp);
+    const int c = static_cast<int>(t / K);
     ss.pi[t] = {1.0, 0.0};
     ss.pi_prev[t] = {1.0, 0.0};
     ss.pi_next[t] = {1.0, 0.0};
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kBlock) void k_ctrl(int K, int Rp, int G, int n, in
     const c128 alpha = s_alpha, tail = s_tail, zs = s_zs;
     long long cnt = 0;
     for (int k = threadIdx.x; k < K; k += kBlock) {
-        const size_t idx = static_cast<size_t>(k) * Rp + c;
+        const size_t idx = shift_at(K, k, c);
         if (ss.last[idx] != kFrozenNever) continue;
         ++cnt;
         const c128 pi = ss.pi[idx], pim = ss.pi_prev[idx];
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(kBlock) void k_post(int K, int Rp, int G, int n, in
     double best = -1.0;
     int bestk = 0x7fffffff, cnt = 0;
     for (int k = threadIdx.x; k < K; k += kBlock) {
-        const size_t idx = static_cast<size_t>(k) * Rp + c;
+        const size_t idx = shift_at(K, k, c);
         if (ss.last[idx] != kFrozenNever) continue;
         const c128 pin = ss.pi_next[idx];
         ss.pi_prev[idx] = ss.pi[idx];
@@ -371,9 +371,9 @@ __global__ __launch_bounds__(kBlock) void k_post(int K, int Rp, int G, int n, in
             cs.done[c] = 1;
         } else {
             const int seed = cs.seed[c];
-            if (ss.last[static_cast<size_t>(seed) * Rp + c] != kFrozenNever) {
+            if (ss.last[shift_at(K, seed, c)] != kFrozenNever) {
                 const int sn = s_k[0];
-                const size_t ix = static_cast<size_t>(sn) * Rp + c;
+                const size_t ix = shift_at(K, sn, c);
                 const c128 cc = ss.pi[ix], ccm = ss.pi_prev[ix];
                 if (full_carry) {
                     // exact seed switch: rescale the seed quantities by pi of
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(kBlock) void k_post(int K, int Rp, int G, int n, in
     if (sw == 1) {
         const c128 cc = s_c, ccm = s_cm;
         for (int k = threadIdx.x; k < K; k += kBlock) {
-            const size_t idx = static_cast<size_t>(k) * Rp + c;
+            const size_t idx = shift_at(K, k, c);
             ss.pi[idx] = cdiv(ss.pi[idx], cc);
             ss.pi_prev[idx] = cdiv(ss.pi_prev[idx], ccm);
             if (ss.dpi != nullptr) {
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kBlock) void k_post(int K, int Rp, int G, int n, in
         }
     } else if (sw == 2) {
         for (int k = threadIdx.x; k < K; k += kBlock) {
-            const size_t idx = static_cast<size_t>(k) * Rp + c;
+            const size_t idx = shift_at(K, k, c);
             if (ss.last[idx] == kFrozenNever) {
                 const c128 pik = ss.pi[idx];
                 if (ss.dpi != nullptr)
@@ -430,8 +430,8 @@ __global__ __launch_bounds__(kBlock) void k_post(int K, int Rp, int G, int n, in
             }
             if (proj_h != nullptr)
                 for (int m = 0; m < M; ++m) {
-                    proj_h[(static_cast<size_t>(k) * Rp + c) * M + m] = {0, 0};
-                    if (proj_dh != nullptr) proj_dh[(static_cast<size_t>(k) * Rp + c) * M + m] = {0, 0};
+                    proj_h[idx * M + m] = {0, 0};
+                    if (proj_dh != nullptr) proj_dh[idx * M + m] = {0, 0};
                 }
         }
     }
@@ -780,7 +780,7 @@ __device__ inline c128 load_coefs(const ShiftState &ss, int k, int col, int tb, 
 // time: lane l holds the step count of shift q*64 + l, and a ballot gives
 // the active ones, so frozen shifts cost nothing.
 struct ActiveShifts {
-    int K, Rp, col, tb, n1, q = -1, st = 0;
+    int K, col, tb, n1, q = -1, st = 0;
     unsigned long long mask = 0;
     const int *last;
     // next active shift (k, its step count) or k = -1
@@ -791,7 +791,7 @@ struct ActiveShifts {
             const int kk = q * 64 + static_cast<int>(threadIdx.x & 63);
             st = 0;
             if (kk < K) {
-                const int l = last[static_cast<size_t>(kk) * Rp + col];
+                const int l = last[shift_at(K, kk, col)];
                 st = (l >= n1 ? n1 : l + 1) - tb;
             }
             mask = __ballot(st > 0);
@@ -811,7 +811,7 @@ struct ActiveShifts {
 // pass.  The next active shift's rows and coefficients are in flight while
 // the current one is updated.
 template <typename T, int M, int E>
-__global__ __launch_bounds__(kBlock) void k_flush(int N, int Rp, int K, int m, int n0, int n1, int only_sw,
+__global__ __launch_bounds__(kBlock) void k_flush(int N, int K, int m, int n0, int n1, int only_sw,
                                                   ColState cs, ShiftState ss,
                                                   const cpx<T> *__restrict__ ringT, size_t ring_ld,
                                                   cpx<T> *__restrict__ X, size_t ldx, cpx<T> *__restrict__ P,
@@ -827,7 +827,7 @@ __global__ __launch_bounds__(kBlock) void k_flush(int N, int Rp, int K, int m, i
     // a pass from step 0 is the column's first: x^k = p^k = 0 before it, so
     // they are not read (nor zeroed beforehand)
     const bool fresh = tb == 0;
-    ActiveShifts act{K, Rp, col, tb, n1};
+    ActiveShifts act{K, col, tb, n1};
     act.last = ss.last;
     int k, kc;
     act.next(k, kc);
@@ -927,7 +927,7 @@ __global__ __launch_bounds__(kBlock) void k_proj_update(int K, int Rp, int Mu, i
     __syncthreads();
     for (int t = threadIdx.x; t < K * M; t += kBlock) {
         const int k = t / M, m = t % M;
-        const size_t idx = static_cast<size_t>(k) * Rp + c;
+        const size_t idx = shift_at(K, k, c);
         if (ss.last[idx] != kFrozenNever) continue;
         const size_t s = coef_at(ss, k, c, slot);
         const size_t o = idx * M + m;
@@ -973,7 +973,7 @@ __global__ __launch_bounds__(kBlock) void k_proj_update_vjp(
         const c128 crm = cr[m];
         c128 ag{0, 0}, ad{0, 0}, az{0, 0};
         for (int k = 0; k < K; ++k) {
-            const size_t idx = static_cast<size_t>(k) * Rp + c;
+            const size_t idx = shift_at(K, k, c);
             if (ss.last[idx] != kFrozenNever) continue;
             const size_t sidx = coef_at(ss, k, c, slot);
             const size_t o = idx * M + m;
@@ -1039,13 +1039,13 @@ __global__ void k_store_cols(int K, int R, int N, const cpx<T> *X, size_t ldk, c
     out[(k * nrhs_total + r0) * N + o] = ccast<double>(X[k * ldk + o]);
 }
 
-__global__ void k_store_proj(int K, int R, int Rp, int M, const c128 *g, c128 *out, int nrhs_total, int r0) {
+__global__ void k_store_proj(int K, int R, int M, const c128 *g, c128 *out, int nrhs_total, int r0) {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t >= static_cast<int64_t>(K) * R * M) return;
     const int m = static_cast<int>(t % M);
     const int c = static_cast<int>((t / M) % R);
     const int k = static_cast<int>(t / (static_cast<int64_t>(M) * R));
-    out[(static_cast<size_t>(k) * nrhs_total + r0 + c) * M + m] = g[(static_cast<size_t>(k) * Rp + c) * M + m];
+    out[(static_cast<size_t>(k) * nrhs_total + r0 + c) * M + m] = g[shift_at(K, k, c) * M + m];
 }
 
 // FP64 true residual ||b - (z_k S - H) x_k||^2 (partial per (k, c) by rows)
@@ -1857,7 +1857,7 @@ template <typename T> class TileSolver {
         } else if (req_.proj_out != nullptr && t_.gacc.get() != nullptr) {
             const int M = t_.Mu + t_.srow;
             const int64_t tot = static_cast<int64_t>(td.K) * td.R * M;
-            k_store_proj<<<div_up(tot, 256), 256, 0, st_>>>(td.K, td.R, td.Rp, M, t_.gacc.get(), req_.proj_out,
+            k_store_proj<<<div_up(tot, 256), 256, 0, st_>>>(td.K, td.R, M, t_.gacc.get(), req_.proj_out,
                                                             nrhs_total, r0_);
             GSC_HIP(hipGetLastError());
         }
@@ -1871,7 +1871,7 @@ template <typename T> class TileSolver {
         GSC_HIP(hipStreamSynchronize(st_));
         for (int k = 0; k < td.K; ++k)
             for (int c = 0; c < td.R; ++c) {
-                const double v = res[static_cast<size_t>(k) * td.Rp + c];
+                const double v = res[shift_at(td.K, k, c)];
                 if (res_host) res_host[static_cast<size_t>(k) * nrhs_total + r0_ + c] = v;
                 if (conv_host) conv_host[static_cast<size_t>(k) * nrhs_total + r0_ + c] = v <= tol ? 1 : 0;
                 worst_res_ = std::max(worst_res_, v);
@@ -2300,7 +2300,7 @@ template <typename T> class TileSolver {
         const size_t NR = static_cast<size_t>(td.N) * td.Rp;
         prof_.begin(st_, KP_SHIFT_UPDATE, 0.0);
 #define GSC_FLUSH(MM)                                                                                        \
-    k_flush<T, MM, E><<<grid, kBlock, 0, st_>>>(td.N, td.Rp, td.K, td.m, n0, n1, only_sw, cs, ss, \
+    k_flush<T, MM, E><<<grid, kBlock, 0, st_>>>(td.N, td.K, td.m, n0, n1, only_sw, cs, ss, \
                                                    t_.ringT.get(), NR, t_.X, ldk_x_, t_.P.get(), t_.ldk, td.R)
         if (td.m <= 1) GSC_FLUSH(1);
         else if (td.m <= 2) GSC_FLUSH(2);
