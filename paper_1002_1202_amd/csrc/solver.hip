@@ -34,19 +34,49 @@ constexpr double kChebBlockBytes = 224.0e6;
 constexpr int kBatchTile = 128;   // default rhs per job of gsc_solve_batched
 
 // ------------------------------------------------------------------ helpers
+__device__ inline double shfl_down(double v, int s) { return __shfl_down(v, s); }
+__device__ inline c128 shfl_down(c128 v, int s) { return {__shfl_down(v.re, s), __shfl_down(v.im, s)}; }
+
+// Sum over the workgroup, in every thread: pairs 128, 64, 32, ... apart.  The
+// per-column kernels below are chains of latencies, not of bytes, so the sums run
+// in one wave's registers (three barriers, not ten), and what k_ctrl reads beside
+// its partials is on its way while they are added up (k_ctrl of 633 Si x 100
+// columns, 101 shifts 8.2 -> 6.5 us, over five systems in a batch 9.7 -> 7.9; the
+// same loads ahead made k_post slower, 8.3 against 13.3).
 template <typename V>
 __device__ inline V block_sum(V v, V *lds) {
+    static_assert(kBlock == 4 * 64, "four waves");
     lds[threadIdx.x] = v;
     __syncthreads();
+    if (threadIdx.x < 64) {
+        v = (v + lds[threadIdx.x + 128]) + (lds[threadIdx.x + 64] + lds[threadIdx.x + 192]);
 #pragma unroll
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) lds[threadIdx.x] = lds[threadIdx.x] + lds[threadIdx.x + s];
-        __syncthreads();
+        for (int s = 32; s > 0; s >>= 1) v = v + shfl_down(v, s);
+        if (threadIdx.x == 0) lds[0] = v;
     }
-    V r = lds[0];
+    __syncthreads();
+    const V r = lds[0];
     __syncthreads();
     return r;
 }
+
+__device__ inline int wave_total(int v) {
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s);
+    return v;
+}
+
+// what the per-column kernels read of a shift
+struct ShiftNow {
+    int last;
+    c128 pi, pi_prev, omega;
+    __device__ void load(const ShiftState &ss, size_t idx) {
+        last = ss.last[idx];
+        pi = ss.pi[idx];
+        pi_prev = ss.pi_prev[idx];
+        omega = ss.omega[idx];
+    }
+};
 
 // Row range of the vector kernels: group g covers rows [g*Lr, (g+1)*Lr).
 #define ELEM_LOOP_BEGIN                                     \
@@ -227,15 +257,18 @@ __global__ __launch_bounds__(kBlock) void k_ctrl(int K, int Rp, int G, int n, in
     __shared__ c128 lds[kBlock];
     __shared__ c128 s_alpha, s_tail, s_zs;
     __shared__ int s_ok;
-    __shared__ long long s_cnt[kBlock];
     const int c = blockIdx.x;
     if (cs.done[c]) return;
+    const c128 rho = cs.rho[c], beta_prev = cs.beta_prev[c], alpha_prev = cs.alpha_prev[c];
+    const int seed = cs.seed[c];
+    const int k0 = threadIdx.x;
+    ShiftNow now{};
+    if (k0 < K) now.load(ss, shift_at(K, k0, c));
     c128 v{0, 0};
     for (int g = threadIdx.x; g < G; g += kBlock) v = v + partial[static_cast<size_t>(g) * Rp + c];
     const c128 mu = block_sum(v, lds);
     if (threadIdx.x == 0) {
         cs.sw[c] = 0;
-        const c128 rho = cs.rho[c];
         const c128 alpha = cdiv(rho, mu);
         int ok = 1;
         if (!cfinite(mu) || !cfinite(alpha)) {
@@ -248,19 +281,20 @@ __global__ __launch_bounds__(kBlock) void k_ctrl(int K, int Rp, int G, int n, in
         if (!ok) cs.done[c] = 1;
         cs.alpha[c] = alpha;
         s_alpha = alpha;
-        s_tail = cdiv(alpha * cs.beta_prev[c], cs.alpha_prev[c]);
-        s_zs = ss.z[cs.seed[c]];
+        s_tail = cdiv(alpha * beta_prev, alpha_prev);
+        s_zs = ss.z[seed];
         s_ok = ok;
     }
     __syncthreads();
     if (!s_ok) return;
     const c128 alpha = s_alpha, tail = s_tail, zs = s_zs;
-    long long cnt = 0;
-    for (int k = threadIdx.x; k < K; k += kBlock) {
+    int cnt = 0;
+    for (int k = k0; k < K; k += kBlock) {
         const size_t idx = shift_at(K, k, c);
-        if (ss.last[idx] != kFrozenNever) continue;
+        if (k != k0) now.load(ss, idx);
+        if (now.last != kFrozenNever) continue;
         ++cnt;
-        const c128 pi = ss.pi[idx], pim = ss.pi_prev[idx];
+        const c128 pi = now.pi, pim = now.pi_prev;
         const c128 delta = ss.z[k] - zs;
         const c128 lead = c128{1.0, 0.0} + alpha * delta;
         const c128 pin = lead * pi + tail * (pi - pim);
@@ -268,32 +302,31 @@ __global__ __launch_bounds__(kBlock) void k_ctrl(int K, int Rp, int G, int n, in
         const c128 q = cdiv(pim, pi);
         const c128 ak = cdiv(alpha * pi, pin);      // alpha^k_n
         ss.ra[coef_at(ss, k, c, slot)] = cdiv(c128{1.0, 0.0}, pi);
-        ss.rb[coef_at(ss, k, c, slot)] = (q * q) * cs.beta_prev[c];
-        ss.rc[coef_at(ss, k, c, slot)] = ss.omega[idx] * ak;
+        ss.rb[coef_at(ss, k, c, slot)] = (q * q) * beta_prev;
+        ss.rc[coef_at(ss, k, c, slot)] = now.omega * ak;
         if (ss.dpi != nullptr) {
             // d/dz_k of the recurrence at a fixed seed process (delta' = 1)
             const c128 dpi = ss.dpi[idx], dpim = ss.dpi_prev[idx];
             const c128 dpin = alpha * pi + lead * dpi + tail * (dpi - dpim);
             ss.dpi_next[idx] = dpin;
             const c128 dak = cdiv(alpha * (dpi * pin - pi * dpin), pin * pin);
-            const c128 dbk = cdiv(2.0 * cs.beta_prev[c] * q * (dpim * pi - pim * dpi), pi * pi);
+            const c128 dbk = cdiv(2.0 * beta_prev * q * (dpim * pi - pim * dpi), pi * pi);
             ss.rda[coef_at(ss, k, c, slot)] = cdiv(c128{-dpi.re, -dpi.im}, pi * pi);
             ss.rdb[coef_at(ss, k, c, slot)] = dbk;
-            ss.rdc[coef_at(ss, k, c, slot)] = ss.domega[idx] * ak + ss.omega[idx] * dak;
+            ss.rdc[coef_at(ss, k, c, slot)] = ss.domega[idx] * ak + now.omega * dak;
         }
     }
-    s_cnt[threadIdx.x] = cnt;
+    __shared__ int s_cnt[kWavesPerBlock];
+    cnt = wave_total(cnt);
+    if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = cnt;
     __syncthreads();
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) s_cnt[threadIdx.x] += s_cnt[threadIdx.x + s];
-        __syncthreads();
-    }
     if (threadIdx.x == 0) {
-        cs.shift_iters[c] += s_cnt[0];
+        const long long active = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+        cs.shift_iters[c] += active;
         cs.iters[c] += 1;
         if (cs.act_hist != nullptr) {
             atomicAdd(reinterpret_cast<unsigned long long *>(cs.act_hist + n),
-                      static_cast<unsigned long long>(s_cnt[0]));
+                      static_cast<unsigned long long>(active));
             atomicAdd(reinterpret_cast<unsigned long long *>(cs.col_hist + n), 1ull);
         }
     }
