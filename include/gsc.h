@@ -285,8 +285,8 @@ gsc_status gsc_spmm(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const double *
  * device memory (code under stream capture, tight serving loops, harnesses
  * that forbid hipMalloc).  The same product and layout; X and Y are DEVICE
  * memory of the context's device, alpha_S HOST [nrhs] complex.  What it has
- * to copy (X, when Y overlaps it and nrhs is not a multiple of 64) goes to
- * one fixed scratch array of 64 MiB per device, part of the library's code
+ * to copy (X, when Y overlaps it and nrhs is not a multiple of 64; the
+ * scalars of more than 512 columns) goes to one fixed scratch array of 64 MiB per device, part of the library's code
  * object and held until the process ends; the call performs no device or
  * pinned-host allocation.  GSC_E_ARG, before any device work, when padded
  * copies of X and Y (nrhs not a multiple of 64) and the columns' scalars

@@ -146,12 +146,12 @@ bool overlap(const void *a, const void *b, size_t bytes) {
 }
 
 // ------------------------------------------------------------------ allocation-free product
-// gsc_spmm_noalloc keeps what it copies (X, when Y overlaps it) in this fixed
-// array instead of allocating: one copy per device, part of the code object, held until the process ends.  In host
-// code the name is only a host-side stand-in, never a device address: host
-// code uses the address hipGetSymbolAddress returns, fetched once per device
-// (with that device current) when a context is created, and kept in the
-// context.
+// gsc_spmm_noalloc keeps what it copies (X, when Y overlaps it; many columns'
+// factors) in this fixed array instead of allocating: one copy per device, part
+// of the code object, held until the process ends.  In host code the name is only
+// a host-side stand-in, never a device address: host code uses the address
+// hipGetSymbolAddress returns, fetched once per device (with that device current)
+// when a context is created, and kept in the context.
 constexpr size_t kScratchBytes = size_t{64} << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -394,7 +394,8 @@ gsc_status gsc_spmm(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const double *
             yout.alloc(n);
             dst = yout.get();
         }
-        launch_product(st, p, nrhs, alpha_S, src, dst);
+        DevBuf<c128> factors(nrhs > kProductFactors ? nrhs : 0);
+        launch_product(st, p, nrhs, alpha_S, src, dst, factors.get());
         if (host)
             GSC_HIP(hipMemcpyAsync(Y, yout.get(), yout.n * sizeof(c128), hipMemcpyDeviceToHost, st));
         GSC_HIP(hipStreamSynchronize(st));
@@ -425,7 +426,7 @@ gsc_status gsc_spmm_noalloc(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const 
             return o;
         };
         const size_t NRp = static_cast<size_t>(N) * Rp;
-        carve(Rp * sizeof(c128));
+        const size_t of = carve(Rp * sizeof(c128));
         carve(Rp * sizeof(int));
         carve(static_cast<size_t>(one_wave_groups(p.nb, Rp / 64)) * Rp * sizeof(c128));
         const size_t ox = ragged ? carve(NRp * sizeof(c128)) : 0;
@@ -434,14 +435,15 @@ gsc_status gsc_spmm_noalloc(gsc_ctx *ctx, const gsc_pair *pair, int nrhs, const 
             throw Error(GSC_E_ARG, "gsc_spmm_noalloc needs " + std::to_string(need) +
                                        " bytes of scratch, more than its maximum of " +
                                        std::to_string(kScratchBytes) + " (fewer rhs or a multiple of 64)");
+        unsigned char *base = static_cast<unsigned char *>(ctx->c.scratch);
         const c128 *src = reinterpret_cast<const c128 *>(X);
         const size_t n = static_cast<size_t>(N) * nrhs;
         if (ragged && overlap(X, Y, n * sizeof(c128))) {
-            c128 *xs = reinterpret_cast<c128 *>(static_cast<unsigned char *>(ctx->c.scratch) + ox);
+            c128 *xs = reinterpret_cast<c128 *>(base + ox);
             GSC_HIP(hipMemcpyAsync(xs, X, n * sizeof(c128), hipMemcpyDeviceToDevice, st));
             src = xs;
         }
-        launch_product(st, p, nrhs, alpha_S, src, reinterpret_cast<c128 *>(Y));
+        launch_product(st, p, nrhs, alpha_S, src, reinterpret_cast<c128 *>(Y), reinterpret_cast<c128 *>(base + of));
         GSC_HIP(hipStreamSynchronize(st));
         return GSC_OK;
     });

@@ -15,7 +15,8 @@ int one_wave_groups(int64_t nb, int chunks);
 // walked by one wave is a chain of 17 to 27 dependent loads (index, then x and
 // S); a quarter of it ends over four times sooner, four times as many waves are
 // there to hide it, and they need fewer rows in flight, whose x stays in L2.
-// Average Chebyshev step of a whole solve, one wave a row -> four: 24 H2O x 192
+// Average Chebyshev step of a whole solve, one wave a row -> four (before the next
+// index was read ahead, see row_blocks): 24 H2O x 192
 // columns 14.9 -> 6.5 us, 256 H2O x 1536 57.5 -> 47.4, 3,000 H2O x 128 (mixed)
 // 34.9 -> 28.4, 633 Si x 128 (mixed) 9.8 -> 6.3, 4,096 Si x 128 32.5 -> 30.0,
 // 4,096 Si x 256 55.2 -> 54.7.  What is left at the large end is the issue of
@@ -199,8 +200,11 @@ template <typename T> inline int seed_split(int nb, int chunks) {
 }
 
 // Y = factor_c S X - H X, X and Y [N][R] of the caller (not overlapping),
-// factors [R] complex in host memory
-void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors, const c128 *X, c128 *Y);
+// factors [R] complex in host memory.  More than kProductFactors columns with
+// factors of their own take one launch and a device copy of the factors in room
+// [R], instead of a launch for each 128 (64 block rows, 1000 columns: 43 against 87 us).
+constexpr int kProductFactors = 512;
+void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors, const c128 *X, c128 *Y, c128 *room);
 
 // with the dots' partials
 template <typename T>

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kBlock) void k_product(int nb, int R, int ncols, co
                                                     const int32_t *__restrict__ colidx,
                                                     const double *__restrict__ Sv, const double *__restrict__ Hv,
                                                     const c128 *__restrict__ X, c128 *__restrict__ Y, int same,
-                                                    Factors f) {
+                                                    const c128 *__restrict__ many, Factors f) {
     constexpr int SPLIT = kSplit<double>;
     __shared__ RowSums<c128, B, SPLIT> red;
     int cx, g;
@@ -94,7 +94,8 @@ __global__ __launch_bounds__(kBlock) void k_product(int nb, int R, int ncols, co
     c128 *y = Y + cx * 64;
     const size_t ld = R;
     const bool act = col < ncols;
-    const c128 z = f.z[same || !act ? 0 : col];
+    const int at = same || !act ? 0 : col;
+    const c128 z = many != nullptr ? many[at] : f.z[at % kFactors];
     struct None {};
     walk_rows<SPLIT, true, false>(
         act, nb, g, w, lane, rowptr, colidx, Sv, Hv, x, ld, red, red, [](size_t) { return None{}; },
@@ -105,14 +106,20 @@ __global__ __launch_bounds__(kBlock) void k_product(int nb, int R, int ncols, co
         [&](size_t row, c128 v, c128, None) { (y + row * ld)[lane] = v; });
 }
 
-void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors, const c128 *X, c128 *Y) {
+void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors, const c128 *X, c128 *Y,
+                    c128 *room) {
     const c128 *z = reinterpret_cast<const c128 *>(factors);
     bool same = true;
     for (int c = 1; c < R && same; ++c) same = std::memcmp(z, z + c, sizeof(c128)) == 0;
+    const c128 *many = nullptr;
+    if (!same && R > kProductFactors) {
+        GSC_HIP(hipMemcpyAsync(room, z, R * sizeof(c128), hipMemcpyHostToDevice, st));
+        many = room;
+    }
     for (int c0 = 0; c0 < R;) {
-        const int n = same ? R : std::min(R - c0, kFactors);
+        const int n = same || many ? R : std::min(R - c0, kFactors);
         Factors f{};
-        std::memcpy(f.z, z + c0, (same ? 1 : n) * sizeof(c128));
+        if (!many) std::memcpy(f.z, z + c0, (same ? 1 : n) * sizeof(c128));
         TileDims td{};
         td.nb = static_cast<int>(pr.nb);
         td.Rp = (n + 63) / 64 * 64;
@@ -120,7 +127,7 @@ void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors
         const dim3 grid(td.Rp / 64, td.Gw);
 #define GSC_PRODUCT(BB)                                                                                           \
     k_product<BB><<<grid, kBlock, 0, st>>>(td.nb, R, n, pr.rowptr.get(), pr.colidx.get(), pr.S.get(), pr.H.get(), \
-                                           X + c0, Y + c0, same, f)
+                                           X + c0, Y + c0, same, many, f)
         if (pr.B == 4) GSC_PRODUCT(4);
         else GSC_PRODUCT(6);
 #undef GSC_PRODUCT

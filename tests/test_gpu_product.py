@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("same", [False, True])
 @pytest.mark.parametrize("entry", ["spmm", "spmm in place", "noalloc", "noalloc in place", "host"])
 @pytest.mark.parametrize("nb,B,R", [(1, 4, 1), (5, 6, 63), (37, 4, 65), (41, 6, 128), (33, 4, 129), (700, 6, 250),
-                                    (4100, 4, 131), (20, 4, 300)])
+                                    (4100, 4, 131), (20, 4, 300), (9, 6, 512), (9, 4, 513), (9, 4, 1025)])
 def test_product_vs_numpy(nb, B, R, entry, same):
     import torch
     from paper_1002_1202_amd import _lib, api
