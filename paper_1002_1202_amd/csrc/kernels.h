@@ -94,8 +94,8 @@ __device__ inline void xcd_remap(int &cx, int &gy) {
 }
 
 // chunk and row group of this workgroup in the gathered products (chunk_order)
-__device__ inline void xcd_remap_chunks(int &cx, int &gy) {
-    chunk_order(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x, gridDim.y, cx, gy);
+__device__ inline void xcd_remap_chunks(bool ragged, int &cx, int &gy) {
+    chunk_order(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x, gridDim.y, ragged, cx, gy);
 }
 
 // loads and stores of streamed (read-once / write-once) vector elements;

@@ -17,7 +17,7 @@
 namespace gsc {
 
 template <typename T, int B, int SPLIT>
-__global__ __launch_bounds__(kBlock) void k_lz_hprod(int nb, int Rp, int Gs,
+__global__ __launch_bounds__(kBlock) void k_lz_hprod(int nb, int Rp, bool ragged, int Gs,
                                                      const int32_t *__restrict__ rowptr,
                                                      const int32_t *__restrict__ colidx, const T *__restrict__ Hv,
                                                      const T *__restrict__ Sv, const cpx<T> *__restrict__ u,
@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kBlock) void k_lz_hprod(int nb, int Rp, int Gs,
     using V = cpx<T>;
     __shared__ RowSums<V, B, SPLIT> redH, redS;
     int cx, g;
-    xcd_remap_chunks(cx, g);
+    xcd_remap_chunks(ragged, cx, g);
     const int lane = threadIdx.x & 63;
     const int wv = wave_id();
     const int col = cx * 64 + lane;
@@ -65,8 +65,9 @@ void launch_lz_hprod(hipStream_t st, const Pair &pr, const TileDims &td, const T
                      cpx<T> *h, cpx<T> *su, const int *skip, double *part) {
     const int split = seed_split<T>(static_cast<int>(pr.nb), td.Rp / 64);
     dim3 grid(td.Rp / 64, td.Gs), block(kBlock);
-#define GSC_LZ(BB, SP)                                                                                        \
-    k_lz_hprod<T, BB, SP><<<grid, block, 0, st>>>(static_cast<int>(pr.nb), td.Rp, td.Gs, pr.rowptr.get(),     \
+    const bool ragged = ragged_end(td.Rp, td.R, 64);
+#define GSC_LZ(BB, SP)                                                                                           \
+    k_lz_hprod<T, BB, SP><<<grid, block, 0, st>>>(static_cast<int>(pr.nb), td.Rp, ragged, td.Gs, pr.rowptr.get(), \
                                                   pr.colidx.get(), Hv, Sv, u, h, su, skip, part)
     if (pr.B == 4) { if (split == 1) GSC_LZ(4, 1); else GSC_LZ(4, kSplit<T>); }
     else { if (split == 1) GSC_LZ(6, 1); else GSC_LZ(6, kSplit<T>); }

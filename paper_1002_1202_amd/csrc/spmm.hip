@@ -35,14 +35,14 @@ __device__ inline void wave_sums_store(P v, P (*red)[64], int w, int lane, P *ou
 // eq. CGp:r with the S-bilinear form) of this row group.
 template <typename T, int B, int SPLIT>
 __global__ __launch_bounds__(kBlock) void k_spmm_seed(
-    int nb, int Rp, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    int nb, int Rp, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ Sv, const T *__restrict__ Hv, const cpx<T> *__restrict__ p,
     cpx<T> *__restrict__ q, const c128 *__restrict__ z, const int *__restrict__ seed,
     const int *__restrict__ skip, c128 *__restrict__ partial) {
     using V = cpx<T>;
     __shared__ RowSums<V, B, SPLIT> red;
     int cx, g;
-    xcd_remap_chunks(cx, g);
+    xcd_remap_chunks(ragged, cx, g);
     const int lane = threadIdx.x & 63;
     const int w = wave_id();
     const int col = cx * 64 + lane;
@@ -78,7 +78,8 @@ __global__ __launch_bounds__(kBlock) void k_spmm_seed(
 constexpr int kFactors = 128;
 struct Factors { c128 z[kFactors]; };
 template <int B>
-__global__ __launch_bounds__(kBlock) void k_product(int nb, int R, int ncols, const int32_t *__restrict__ rowptr,
+__global__ __launch_bounds__(kBlock) void k_product(int nb, int R, int ncols, bool ragged,
+                                                    const int32_t *__restrict__ rowptr,
                                                     const int32_t *__restrict__ colidx,
                                                     const double *__restrict__ Sv, const double *__restrict__ Hv,
                                                     const c128 *__restrict__ X, c128 *__restrict__ Y, int same,
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(kBlock) void k_product(int nb, int R, int ncols, co
     constexpr int SPLIT = kSplit<double>;
     __shared__ RowSums<c128, B, SPLIT> red;
     int cx, g;
-    xcd_remap_chunks(cx, g);
+    xcd_remap_chunks(ragged, cx, g);
     const int lane = threadIdx.x & 63;
     const int w = wave_id();
     const int col = cx * 64 + lane;
@@ -125,9 +126,10 @@ void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors
         td.Rp = (n + 63) / 64 * 64;
         set_spmm_geometry(td, false);
         const dim3 grid(td.Rp / 64, td.Gw);
+        const bool ragged = ragged_end(td.Rp, n, 64);
 #define GSC_PRODUCT(BB)                                                                                           \
-    k_product<BB><<<grid, kBlock, 0, st>>>(td.nb, R, n, pr.rowptr.get(), pr.colidx.get(), pr.S.get(), pr.H.get(), \
-                                           X + c0, Y + c0, same, many, f)
+    k_product<BB><<<grid, kBlock, 0, st>>>(td.nb, R, n, ragged, pr.rowptr.get(), pr.colidx.get(), pr.S.get(),  \
+                                           pr.H.get(), X + c0, Y + c0, same, many, f)
         if (pr.B == 4) GSC_PRODUCT(4);
         else GSC_PRODUCT(6);
 #undef GSC_PRODUCT
@@ -140,7 +142,7 @@ void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors
 // per-column partial  Re(d^H S d)  (the CG curvature; S real symmetric).
 template <typename T, int B>
 __global__ __launch_bounds__(kBlock) void k_spmm_S(
-    int nb, int Rp, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    int nb, int Rp, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ Sv, const cpx<T> *__restrict__ d, cpx<T> *__restrict__ wout,
     const int *__restrict__ skip, double *__restrict__ partial) {
     using V = cpx<T>;
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_S(
     __shared__ RowSums<V, B, SPLIT> red;
     __shared__ double redd[kWavesPerBlock][64];
     int cx, g;
-    xcd_remap_chunks(cx, g);
+    xcd_remap_chunks(ragged, cx, g);
     const int lane = threadIdx.x & 63;
     const int w = wave_id();
     const int col = cx * 64 + lane;
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(kBlock) void k_spmm_S(
 // (dot_active_only = 0) or only for the columns that take this step.
 template <typename T, int B, int MODE, bool NT, int OUT>
 __global__ __launch_bounds__(kBlock) void k_cheb_step(
-    int nb, int Rp, int col0, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    int nb, int Rp, int col0, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ Sv, const cpx<T> *__restrict__ y, const cpx<T> *__restrict__ r,
     cpx<T> *__restrict__ yio, const int *__restrict__ skip, T inv_theta, T c1, T c2,
     double *__restrict__ partial, c128 *__restrict__ dpart, int dot_active_only) {
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(kBlock) void k_cheb_step(
     constexpr int SPLIT = kSplit<T>;
     __shared__ RowSums<V, B, SPLIT> red;
     int cx, g;
-    xcd_remap_chunks(cx, g);
+    xcd_remap_chunks(ragged, cx, g);
     const int lane = threadIdx.x & 63;
     const int w = wave_id();
     const int cb = col0 + cx * 64, col = cb + lane;
@@ -234,10 +236,11 @@ void launch_cheb_step(hipStream_t st, const Pair &pr, const TileDims &td, int mo
                 "Chebyshev column block outside the tile");
     GSC_REQUIRE(dot_mode == 0 || (dpart != nullptr && partial != nullptr), "the fused dot needs its partials");
     dim3 grid(ncols / 64, partial ? td.Gs : kSplit<T> == 1 ? td.G1 : td.Gw), block(kBlock);
+    const bool ragged = ragged_end(col0 + ncols, td.R, 64);
     const T it = static_cast<T>(inv_theta), a = static_cast<T>(c1), b = static_cast<T>(c2);
 #define GSC_CHEB_D(BB, M, N, D)                                                                                   \
-    k_cheb_step<T, BB, M, N, D><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, pr.rowptr.get(), pr.colidx.get(), Sv, \
-                                                        y, r, yio, skip, it, a, b, partial, dpart, dot_mode == 2)
+    k_cheb_step<T, BB, M, N, D><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, ragged, pr.rowptr.get(),               \
+                                                        pr.colidx.get(), Sv, y, r, yio, skip, it, a, b, partial, dpart, dot_mode == 2)
 #define GSC_CHEB(BB, M, N) \
     if (dot_mode) GSC_CHEB_D(BB, M, N, 2); else if (partial) GSC_CHEB_D(BB, M, N, 1); else GSC_CHEB_D(BB, M, N, 0);
 #define GSC_CHEB_N(BB, M) \
@@ -285,7 +288,7 @@ template <> struct mx_lane<c64x2> {
 
 template <typename V, int B, int MODE, int FIN, int OUT>
 __global__ __launch_bounds__(kBlock) void k_cheb_mx(
-    int nb, int Rp, int col0, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    int nb, int Rp, int col0, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const float *__restrict__ Sv, const c64 *__restrict__ y, const c64 *__restrict__ f, c64 *__restrict__ yio,
     c128 *__restrict__ Y, const c128 *__restrict__ r, const int *__restrict__ skip, float inv_theta, float c1,
     float c2, double *__restrict__ partial, c128 *__restrict__ dpart, int dot_active_only) {
@@ -293,7 +296,7 @@ __global__ __launch_bounds__(kBlock) void k_cheb_mx(
     constexpr int W = L::W, SPLIT = kWavesPerBlock;
     __shared__ RowSums<V, B, SPLIT> red;
     int cx, g;
-    xcd_remap_chunks(cx, g);
+    xcd_remap_chunks(ragged, cx, g);
     const int lane = threadIdx.x & 63;
     const int w = wave_id();
     const int cb = col0 + cx * 64 * W, col = cb + W * lane;
@@ -368,14 +371,14 @@ __global__ __launch_bounds__(kBlock) void k_cheb_mx(
 // right-hand side of the next complex64 round.
 template <int B>
 __global__ __launch_bounds__(kBlock) void k_mx_resid(
-    int nb, int Rp, int col0, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
+    int nb, int Rp, int col0, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const double *__restrict__ Sv, const c128 *__restrict__ Y, const c128 *__restrict__ r, c64 *__restrict__ f,
     const int *__restrict__ skip) {
     using V = c128;
     constexpr int SPLIT = kWavesPerBlock;
     __shared__ RowSums<V, B, SPLIT> red;
     int cx, g;
-    xcd_remap_chunks(cx, g);
+    xcd_remap_chunks(ragged, cx, g);
     const int lane = threadIdx.x & 63;
     const int w = wave_id();
     const int cb = col0 + cx * 64;
@@ -402,8 +405,8 @@ void launch_cheb_mx(hipStream_t st, const Pair &pr, const TileDims &td, int mode
     // 128-column pieces with two columns per lane, a 64-column tail with one
     const int n2 = ncols / 128 * 128;
 #define GSC_MX(V, BB, M, F, O)                                                                                    \
-    k_cheb_mx<V, BB, M, F, O><<<grid, kBlock, 0, st>>>(td.nb, td.Rp, c0, pr.rowptr.get(), pr.colidx.get(), Sv, y, \
-                                                       f, yio, Y, r, skip, it, a, b, partial, dpart, dot_active_only)
+    k_cheb_mx<V, BB, M, F, O><<<grid, kBlock, 0, st>>>(td.nb, td.Rp, c0, ragged, pr.rowptr.get(),                 \
+                                                       pr.colidx.get(), Sv, y, f, yio, Y, r, skip, it, a, b, partial, dpart, dot_active_only)
 #define GSC_MX_O(V, BB, M, F) \
     if (dot) GSC_MX(V, BB, M, F, 2); else if (partial) GSC_MX(V, BB, M, F, 1); else GSC_MX(V, BB, M, F, 0);
 #define GSC_MX_F(V, BB, M)                   \
@@ -416,11 +419,13 @@ void launch_cheb_mx(hipStream_t st, const Pair &pr, const TileDims &td, int mode
     if (n2 > 0) {
         const dim3 grid(n2 / 128, G);
         const int c0 = col0;
+        const bool ragged = ragged_end(c0 + n2, td.R, 128);
         GSC_MX_B(c64x2)
     }
     if (n2 < ncols) {
         const dim3 grid((ncols - n2) / 64, G);
         const int c0 = col0 + n2;
+        const bool ragged = ragged_end(col0 + ncols, td.R, 64);
         GSC_MX_B(c64)
     }
 #undef GSC_MX_B
@@ -436,11 +441,12 @@ void launch_mx_resid(hipStream_t st, const Pair &pr, const TileDims &td, int col
     GSC_REQUIRE(col0 % 64 == 0 && ncols % 64 == 0 && ncols > 0 && col0 + ncols <= td.Rp,
                 "Chebyshev column block outside the tile");
     dim3 grid(ncols / 64, td.Gw), block(kBlock);
+    const bool ragged = ragged_end(col0 + ncols, td.R, 64);
     if (pr.B == 4)
-        k_mx_resid<4><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, pr.rowptr.get(), pr.colidx.get(), Sv, Y, r, f,
+        k_mx_resid<4><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, ragged, pr.rowptr.get(), pr.colidx.get(), Sv, Y, r, f,
                                               skip);
     else
-        k_mx_resid<6><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, pr.rowptr.get(), pr.colidx.get(), Sv, Y, r, f,
+        k_mx_resid<6><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, ragged, pr.rowptr.get(), pr.colidx.get(), Sv, Y, r, f,
                                               skip);
     GSC_HIP(hipGetLastError());
 }
@@ -484,9 +490,10 @@ void launch_spmm_seed(hipStream_t st, const Pair &pr, const TileDims &td, const 
                       c128 *partial) {
     const int split = seed_split<T>(td.nb, td.Rp / 64);
     dim3 grid(td.Rp / 64, td.Gs), block(kBlock);
+    const bool ragged = ragged_end(td.Rp, td.R, 64);
 #define GSC_SEED(BB, SP)                                                                                         \
-    k_spmm_seed<T, BB, SP><<<grid, block, 0, st>>>(td.nb, td.Rp, pr.rowptr.get(), pr.colidx.get(), Sv, Hv, p, q, \
-                                                   z, seed, skip, partial)
+    k_spmm_seed<T, BB, SP><<<grid, block, 0, st>>>(td.nb, td.Rp, ragged, pr.rowptr.get(), pr.colidx.get(), Sv, Hv,   \
+                                                   p, q, z, seed, skip, partial)
 #define GSC_SEED_S(BB) \
     if (split == 1) GSC_SEED(BB, 1); else GSC_SEED(BB, kSplit<T>);
     if (pr.B == 4) { GSC_SEED_S(4) } else { GSC_SEED_S(6) }
@@ -499,11 +506,12 @@ template <typename T>
 void launch_spmm_S(hipStream_t st, const Pair &pr, const TileDims &td, const T *Sv, const cpx<T> *d,
                    cpx<T> *w, const int *skip, double *partial) {
     dim3 grid(td.Rp / 64, td.Gs), block(kBlock);
+    const bool ragged = ragged_end(td.Rp, td.R, 64);
     if (pr.B == 4)
-        k_spmm_S<T, 4><<<grid, block, 0, st>>>(td.nb, td.Rp, pr.rowptr.get(), pr.colidx.get(), Sv,
+        k_spmm_S<T, 4><<<grid, block, 0, st>>>(td.nb, td.Rp, ragged, pr.rowptr.get(), pr.colidx.get(), Sv,
                                                d, w, skip, partial);
     else
-        k_spmm_S<T, 6><<<grid, block, 0, st>>>(td.nb, td.Rp, pr.rowptr.get(), pr.colidx.get(), Sv,
+        k_spmm_S<T, 6><<<grid, block, 0, st>>>(td.nb, td.Rp, ragged, pr.rowptr.get(), pr.colidx.get(), Sv,
                                                d, w, skip, partial);
     GSC_HIP(hipGetLastError());
 }
