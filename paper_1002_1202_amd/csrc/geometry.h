@@ -2,6 +2,9 @@
 // can be checked without a device.
 #pragma once
 
+#include <algorithm>
+#include <cstdint>
+
 #ifdef __HIPCC__
 #define GSC_HOST_DEVICE __host__ __device__
 #else
@@ -59,5 +62,86 @@ GSC_HOST_DEVICE inline void chunk_order(int l, int gx, int G, bool ragged, int &
 // columns, as a ragged and as a full one: 256 H2O 64.4 | 63.1 ms, 3,000 H2O 489 |
 // 484; of 48: 63.7 | 63.4, 483 | 486; of 32: 62.6 | 62.4, 463 | 474).
 GSC_HOST_DEVICE inline bool ragged_end(int end, int R, int width) { return 4 * (end - R) >= width; }
+
+// ------------------------------------------------------------------ row groups
+inline int up8(int64_t g) { return static_cast<int>((std::min<int64_t>(g, 65528) + 7) / 8 * 8); }
+
+// Groups of four block rows (one wave each): one row a wave while a launch
+// stays within 16384 workgroups, else about 4096 workgroups with equal rows
+// per wave, at least 256 groups when there are more than 8 column chunks (an
+// XCD would otherwise run the groups of several chunks at once).
+inline int one_wave_groups(int64_t nb, int chunks) {
+    const int64_t slots = std::max<int64_t>(1, (nb + 3) / 4);
+    int64_t g = slots;
+    if (chunks * slots > 16384) {
+        int64_t g0 = std::max(1, 4096 / chunks);
+        if (chunks > 8) g0 = std::max<int64_t>(g0, 256);
+        g0 = std::min(g0, slots);
+        const int64_t passes = (slots + g0 - 1) / g0;
+        g = (slots + passes - 1) / passes;
+    }
+    return up8(g);
+}
+
+// Row groups (multiples of 8) of the product launches: a group is one workgroup a
+// column chunk and takes a block row (four with one wave a row) in turn, every Gth.
+struct RowGroups {
+    int Gs;       // launches with one matrix that leave partial sums per group and column
+    int Gw;       // launches that leave none and share a row
+    int G1;       // launches that leave none, one wave a row
+    int G2;       // launches with two matrices (the seed and Lanczos products), with partial sums
+    int waves2;   // waves they give a row, four or one
+};
+
+// Whether block rows are long: a wave gathers row_orbitals (stored blocks times B)
+// orbital rows of x for one.  Measured at 68 (Si, 17 blocks of 4) and 162 (water, 27
+// of 6); the line lies between.
+inline bool long_rows(int64_t row_orbitals) { return row_orbitals >= 112; }
+
+// Waves that the products with two matrices (S and H: the seed product, the
+// Lanczos product) give a block row.  Their two sums a lane leave 5 waves on a
+// SIMD against 8, so once there are enough rows to fill the card twice over, one
+// wave a row is ahead (microseconds, one wave / four: 4,096 Si x 256 columns 80 /
+// 88, 4,096 Si x 128 45.9 / 47.8; but 256 H2O x 1536 108 / 83, 3,000 H2O x 128
+// 136 / 89, 24 H2O x 192 20.5 / 9.2).
+inline int product_waves(int64_t nb, int chunks) { return nb * chunks >= 8192 ? 1 : 4; }
+
+// Waves that a launch of Chebyshev steps (or of their residuals) gives a block row;
+// narrow: complex64 with one column a lane.  Four, except for short rows in launches
+// of one chunk with enough rows: the waves of one chunk then fill the card without
+// sharing, whose LDS pass and barriers are left as cost.  60 (member of N 76,152:
+// 120) iterations with 64 columns a launch, ms in the steps, four / one: FP64 N
+// 76,152 462 / 455, N 122,196 318 / 314, N 131,072 571 / 556; mixed 290 / 279, 210 /
+// 199, 318 / 292, their FP64 residuals 62 / 60, 43 / 41, 79 / 75.  Below, whole runs
+// of 30 iterations, four / one: FP64 12,288 rows 30.4 / 29.9 ms, 8,192 rows 19.2 /
+// 19.9; mixed 4,096 rows 12.2 / 11.7, 2,048 rows the same.  Two chunks and more, or
+// two columns a lane, mixed: 8,192 rows x 128 columns 27.0 / 29.2.  Long rows, 12,000
+// H2O x 64 columns: FP64 62 / 67, mixed 51 / 55.
+inline int step_waves(int64_t nb, int chunks, int64_t row_orbitals, bool narrow) {
+    return !long_rows(row_orbitals) && chunks == 1 && nb >= (narrow ? 4096 : 12288) ? 1 : 4;
+}
+
+// For a tile of `chunks` column chunks, `width` of them in a Chebyshev launch;
+// one_wave: every launch gives a row one wave.  Launches that leave no partial sums
+// give every block row its own workgroup (1, 2, 4 and 8 rows a workgroup on the
+// Chebyshev step: 4,096 Si x 128 columns 35.8 / 38.2 / 40.8 / 35.6 us, 2,668 Si x
+// 128 25.2 / 27.7 / 29.5 / 31.8, 64 H2O x 384 9.5 / 11.9 / 18.7 / 35.5).  Those that
+// leave them take up to four rows a group, as many as bring the groups to about 1024
+// (the reductions read every group's value of every column), and never more: with
+// 1024 groups whatever the rows, a launch of one chunk is too small for the card (N
+// 131,072: seed product 75 -> 115 us a launch of 8 chunks).  Fewer rows a group than
+// that, 4 / 2 / 1 at 8,192 rows x 128 columns 30.7 / 32.5 / 36.9 ms a run.  One wave
+// a row never takes more groups than that needs: the groups beyond the last row
+// would be whole XCDs' share (2,048 Si x 256 columns, seed product 63 -> 47 us).
+inline RowGroups row_groups(int64_t nb, int chunks, int width, bool one_wave) {
+    RowGroups g;
+    g.G1 = one_wave_groups(nb, width);
+    g.Gw = up8(nb);
+    const int64_t rows = std::min<int64_t>(4, (nb + 1023) / 1024);
+    g.Gs = one_wave || rows == 4 ? g.G1 : up8((nb + rows - 1) / rows);
+    g.waves2 = one_wave ? 1 : product_waves(nb, chunks);
+    g.G2 = g.waves2 == 1 ? g.G1 : g.Gs;
+    return g;
+}
 
 }  // namespace gsc

@@ -66,16 +66,11 @@ __host__ __device__ inline size_t coef_at(const ShiftState &ss, int k, int c, in
     return (static_cast<size_t>(c) * ss.cK + k) * ss.cm + slot;
 }
 
-struct TileDims {
+struct TileDims : RowGroups {     // row groups of the product launches
     int N, nb, B, K, R, Rp, m;
     int G;                    // row groups of the vector kernels (multiple of 8)
     int Lr;                   // rows per group (vector kernels)
-    // row groups of the product launches (multiples of 8): a group is one
-    // workgroup a column chunk and takes a block row (four with one wave a
-    // row) in turn, every Gth
-    int Gs;                   // launches that leave partial sums per group and column
-    int Gw;                   // launches that leave none and share a row
-    int G1;                   // launches that leave none, one wave a row
+    int row_orbitals;         // orbital rows of x that an average block row gathers
     bool nt = false;          // streamed vectors of the Chebyshev step bypass L2 retention
     int cb = 0;               // columns per Chebyshev column block (multiple of 64; Rp: one block)
 };

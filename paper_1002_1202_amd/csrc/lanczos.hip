@@ -17,7 +17,7 @@
 namespace gsc {
 
 template <typename T, int B, int SPLIT>
-__global__ __launch_bounds__(kBlock) void k_lz_hprod(int nb, int Rp, bool ragged, int Gs,
+__global__ __launch_bounds__(kBlock) void k_lz_hprod(int nb, int Rp, bool ragged, int G2,
                                                      const int32_t *__restrict__ rowptr,
                                                      const int32_t *__restrict__ colidx, const T *__restrict__ Hv,
                                                      const T *__restrict__ Sv, const cpx<T> *__restrict__ u,
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kBlock) void k_lz_hprod(int nb, int Rp, bool ragged
             double t = 0.0;
 #pragma unroll
             for (int k = 0; k < kWavesPerBlock; ++k) t += red[q][k][lane];
-            part[(static_cast<size_t>(q) * Gs + g) * Rp + col] = t;
+            part[(static_cast<size_t>(q) * G2 + g) * Rp + col] = t;
         }
     }
 }
@@ -63,14 +63,13 @@ __global__ __launch_bounds__(kBlock) void k_lz_hprod(int nb, int Rp, bool ragged
 template <typename T>
 void launch_lz_hprod(hipStream_t st, const Pair &pr, const TileDims &td, const T *Hv, const T *Sv, const cpx<T> *u,
                      cpx<T> *h, cpx<T> *su, const int *skip, double *part) {
-    const int split = seed_split<T>(static_cast<int>(pr.nb), td.Rp / 64);
-    dim3 grid(td.Rp / 64, td.Gs), block(kBlock);
+    dim3 grid(td.Rp / 64, td.G2), block(kBlock);
     const bool ragged = ragged_end(td.Rp, td.R, 64);
 #define GSC_LZ(BB, SP)                                                                                           \
-    k_lz_hprod<T, BB, SP><<<grid, block, 0, st>>>(static_cast<int>(pr.nb), td.Rp, ragged, td.Gs, pr.rowptr.get(), \
+    k_lz_hprod<T, BB, SP><<<grid, block, 0, st>>>(static_cast<int>(pr.nb), td.Rp, ragged, td.G2, pr.rowptr.get(), \
                                                   pr.colidx.get(), Hv, Sv, u, h, su, skip, part)
-    if (pr.B == 4) { if (split == 1) GSC_LZ(4, 1); else GSC_LZ(4, kSplit<T>); }
-    else { if (split == 1) GSC_LZ(6, 1); else GSC_LZ(6, kSplit<T>); }
+    if (pr.B == 4) { if (td.waves2 == 1) GSC_LZ(4, 1); else GSC_LZ(4, kSplit<T>); }
+    else { if (td.waves2 == 1) GSC_LZ(6, 1); else GSC_LZ(6, kSplit<T>); }
 #undef GSC_LZ
     GSC_HIP(hipGetLastError());
 }

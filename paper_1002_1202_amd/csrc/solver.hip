@@ -1197,14 +1197,14 @@ __global__ __launch_bounds__(kBlock) void k_lz_start(int N, int Rp, int Lr, cons
 }
 
 // a_n = u^T H u of both processes of a column from the product's partials
-__global__ __launch_bounds__(kBlock) void k_lz_reduce_a(int Rp, int Gs, const double *part, int n, int mmax,
+__global__ __launch_bounds__(kBlock) void k_lz_reduce_a(int Rp, int G2, const double *part, int n, int mmax,
                                                         double *a, int *steps, const int *done) {
     __shared__ double lds[kBlock];
     const int c = blockIdx.x;
     double s0 = 0.0, s1 = 0.0;
-    for (int g = threadIdx.x; g < Gs; g += kBlock) {
+    for (int g = threadIdx.x; g < G2; g += kBlock) {
         s0 += part[static_cast<size_t>(g) * Rp + c];
-        s1 += part[(static_cast<size_t>(Gs) + g) * Rp + c];
+        s1 += part[(static_cast<size_t>(G2) + g) * Rp + c];
     }
     s0 = block_sum(s0, lds);
     s1 = block_sum(s1, lds);
@@ -1446,12 +1446,12 @@ template <typename T> class TileSolver {
             const bool huge = autob && cb < 128;
             if (huge) cb = 64;
             td.cb = (cb >= 64 && cb < Rp) ? cb : Rp;
-            set_spmm_geometry(td, kSplit<T> == 1);
+            set_spmm_geometry(td, pr_, kSplit<T> == 1);
             if (req.opts.row_groups > 0) {
                 // caller's row groups, at most one block row a workgroup (a
                 // wave in the all-complex64 process)
                 const int cap = kSplit<T> == 1 ? (td.nb + 3) / 4 : td.nb;
-                td.Gs = td.Gw = td.G1 = (std::min(req.opts.row_groups, cap) + 7) / 8 * 8;
+                td.Gs = td.Gw = td.G1 = td.G2 = (std::min(req.opts.row_groups, cap) + 7) / 8 * 8;
             }
             td.nt = req.opts.stream_hint == 2 || (req.opts.stream_hint == 0 && huge);
         }
@@ -1489,7 +1489,7 @@ template <typename T> class TileSolver {
         t_.s_pi.alloc(KR); t_.s_pi_prev.alloc(KR); t_.s_pi_next.alloc(KR); t_.s_omega.alloc(KR);
         t_.s_res.alloc(KR); t_.s_last.alloc(KR);
         t_.s_ra.alloc(KR * td.m); t_.s_rb.alloc(KR * td.m); t_.s_rc.alloc(KR * td.m);
-        const size_t G = std::max(td.G, td.Gs);
+        const size_t G = std::max({td.G, td.Gs, td.G2});
         t_.part_c.alloc(G * Rp);
         t_.part_d.alloc(G * Rp);
         if (full_) {
@@ -1586,7 +1586,7 @@ template <typename T> class TileSolver {
         cpx<T> *rp = t_.ring.get();   // m = 1 for the projected carry
         launch_spmm_seed<T>(st_, pr_, td, Sv, Hv, t_.p.get(), t_.q.get(), dz_, t_.c_seed.get(), t_.c_done.get(),
                             t_.part_c.get());
-        k_ctrl<<<td.Rp, kBlock, 0, st_>>>(td.K, td.Rp, td.Gs, n, 0, t_.part_c.get(), cs, ss);
+        k_ctrl<<<td.Rp, kBlock, 0, st_>>>(td.K, td.Rp, td.G2, n, 0, t_.part_c.get(), cs, ss);
         proj_update(cs, ss, 0, rp);
         k_update_r<T><<<eg, eb, 0, st_>>>(td.N, td.Rp, td.Lr, t_.c_done.get(), t_.c_alpha.get(), t_.q.get(),
                                          t_.r.get(), t_.res.get(), t_.d.get(), t_.part_d.get(), cheb_ok_ ? 0 : 1,
@@ -1642,7 +1642,7 @@ template <typename T> class TileSolver {
                                 t_.c_done.get(), t_.part_c.get());
             prof_.end(st_);
             prof_.begin(st_, KP_CTRL, 0.0);
-            k_ctrl<<<td.Rp, kBlock, 0, st_>>>(td.K, td.Rp, td.Gs, n, slot, t_.part_c.get(), cs, ss);
+            k_ctrl<<<td.Rp, kBlock, 0, st_>>>(td.K, td.Rp, td.G2, n, slot, t_.part_c.get(), cs, ss);
             prof_.end(st_);
             if (full_) {
                 if (n + 1 - n0 == td.m) {
@@ -1757,7 +1757,7 @@ template <typename T> class TileSolver {
         const dim3 eg(td.Rp / 64, td.G), eb(kBlock);
         const int cb = div_up(td.Rp, 256);
         const size_t NR = static_cast<size_t>(td.N) * td.Rp;
-        const int Gm = std::max(td.G, td.Gs);
+        const int Gm = std::max(td.G, td.G2);
         DevBuf<double> part(3 * static_cast<size_t>(Gm) * td.Rp), inv(2 * static_cast<size_t>(td.Rp));
         DevBuf<int> done(2 * static_cast<size_t>(td.Rp));
         DevBuf<c128> gprev(static_cast<size_t>(std::max(P, 1)) * td.K);
@@ -1780,16 +1780,16 @@ template <typename T> class TileSolver {
         GSC_HIP(hipGetLastError());
         check_status(false);
         const T *Hv = hval(), *Sv = sval();
-        const size_t Gs = static_cast<size_t>(td.Gs);
+        const size_t G2 = static_cast<size_t>(td.G2);
         int ran = 0;
         for (int n = 0; n < mmax; ++n) {
             prof_.begin(st_, KP_LZ_HPROD, 2.0 * mat_bytes() + 3.0 * last_active_ * td.N * sizeof(cpx<T>));
             launch_lz_hprod<T>(st_, pr_, td, Hv, Sv, u, t_.r.get(), s, cs.done, part.get());
             prof_.end(st_);
-            k_lz_reduce_a<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, part.get(), n, mmax, a, steps, done.get());
+            k_lz_reduce_a<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.G2, part.get(), n, mmax, a, steps, done.get());
             ran = n + 1;
             if (n == mmax - 1) break;
-            k_col_rnorm<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, part.get() + 2 * Gs * td.Rp, 0, inner_tol, cs);
+            k_col_rnorm<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.G2, part.get() + 2 * G2 * td.Rp, 0, inner_tol, cs);
             if (!cheb_ok_) {
                 k_copy_vec<T><<<div_up(NR, 256), 256, 0, st_>>>(NR, t_.r.get(), t_.res.get());
                 k_copy_vec<T><<<div_up(NR, 256), 256, 0, st_>>>(NR, t_.r.get(), t_.d.get());
@@ -2281,9 +2281,13 @@ template <typename T> class TileSolver {
         prof_.end_group(st_, launches, bytes);
         k_cheb_check<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, t_.part_d.get(), inner_tol_ / cheb_rho_, 0, cs);
         // extra steps for the columns that failed the check (bytes counted
-        // from the check's outcome are not known here: counted as zero)
+        // from the check's outcome are not known here: counted as zero).  There
+        // are hardly ever any, and a launch with a workgroup for each row that
+        // finds nothing to do takes 35 to 45 us (32,768 rows x 508 columns, 19,038
+        // x 332): both steps take the groups of those that leave partials, the
+        // second overwrites the first's
         prof_.begin_group(st_, KP_CHEB);
-        step(K, t_.c_inner_done.get(), 0, td.Rp, false, 0);
+        step(K, t_.c_inner_done.get(), 0, td.Rp, true, 0);
         step(K + 1, t_.c_inner_done.get(), 0, td.Rp, true, 2);
         prof_.end_group(st_, 2, 0.0);
         k_cheb_check<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, t_.part_d.get(), inner_tol_, 1, cs);

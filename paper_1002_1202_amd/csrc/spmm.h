@@ -5,8 +5,7 @@ namespace gsc {
 
 // row groups (TileDims) of the product kernels; one_wave: all of them walk a
 // block row with one wave (kSplit 1)
-void set_spmm_geometry(TileDims &td, bool one_wave);
-int one_wave_groups(int64_t nb, int chunks);
+void set_spmm_geometry(TileDims &td, const Pair &pr, bool one_wave);
 
 // ------------------------------------------------------------------ one block row in a workgroup
 // The four waves of a workgroup share one block row at a time: each takes a
@@ -188,16 +187,6 @@ __device__ inline void walk_rows(bool act, int nb, int g, int w, int lane, const
 struct NoCombine {
     template <typename A> __device__ void operator()(A &, A &) const {}
 };
-
-// Waves that the products with two matrices (S and H: the seed product, the
-// Lanczos product) give a block row.  Their two sums a lane leave 5 waves on a
-// SIMD against 8, so once there are enough rows to fill the card twice over, one
-// wave a row is ahead (microseconds, one wave / four: 4,096 Si x 256 columns 80 /
-// 88, 4,096 Si x 128 45.9 / 47.8; but 256 H2O x 1536 108 / 83, 3,000 H2O x 128
-// 136 / 89, 24 H2O x 192 20.5 / 9.2).
-template <typename T> inline int seed_split(int nb, int chunks) {
-    return kSplit<T> == 1 || static_cast<int64_t>(nb) * chunks >= 8192 ? 1 : kSplit<T>;
-}
 
 // Y = factor_c S X - H X, X and Y [N][R] of the caller (not overlapping),
 // factors [R] complex in host memory.  More than kProductFactors columns with

@@ -124,7 +124,7 @@ void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors
         TileDims td{};
         td.nb = static_cast<int>(pr.nb);
         td.Rp = (n + 63) / 64 * 64;
-        set_spmm_geometry(td, false);
+        set_spmm_geometry(td, pr, false);
         const dim3 grid(td.Rp / 64, td.Gw);
         const bool ragged = ragged_end(td.Rp, n, 64);
 #define GSC_PRODUCT(BB)                                                                                           \
@@ -179,14 +179,13 @@ __global__ __launch_bounds__(kBlock) void k_spmm_S(
 // the partial of y_{k+1}^T r (unconjugated: the next rho of the outer
 // iteration, eq. CGp:p) goes to dpart as well, for every column
 // (dot_active_only = 0) or only for the columns that take this step.
-template <typename T, int B, int MODE, bool NT, int OUT>
+template <typename T, int B, int SPLIT, int MODE, bool NT, int OUT>
 __global__ __launch_bounds__(kBlock) void k_cheb_step(
     int nb, int Rp, int col0, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ Sv, const cpx<T> *__restrict__ y, const cpx<T> *__restrict__ r,
     cpx<T> *__restrict__ yio, const int *__restrict__ skip, T inv_theta, T c1, T c2,
     double *__restrict__ partial, c128 *__restrict__ dpart, int dot_active_only) {
     using V = cpx<T>;
-    constexpr int SPLIT = kSplit<T>;
     __shared__ RowSums<V, B, SPLIT> red;
     int cx, g;
     xcd_remap_chunks(ragged, cx, g);
@@ -235,20 +234,28 @@ void launch_cheb_step(hipStream_t st, const Pair &pr, const TileDims &td, int mo
     GSC_REQUIRE(col0 % 64 == 0 && ncols % 64 == 0 && ncols > 0 && col0 + ncols <= td.Rp,
                 "Chebyshev column block outside the tile");
     GSC_REQUIRE(dot_mode == 0 || (dpart != nullptr && partial != nullptr), "the fused dot needs its partials");
-    dim3 grid(ncols / 64, partial ? td.Gs : kSplit<T> == 1 ? td.G1 : td.Gw), block(kBlock);
+    const int waves = kSplit<T> == 1 ? 1 : step_waves(td.nb, ncols / 64, td.row_orbitals, false);
+    dim3 grid(ncols / 64, partial ? td.Gs : waves == 1 ? td.G1 : td.Gw), block(kBlock);
     const bool ragged = ragged_end(col0 + ncols, td.R, 64);
     const T it = static_cast<T>(inv_theta), a = static_cast<T>(c1), b = static_cast<T>(c2);
-#define GSC_CHEB_D(BB, M, N, D)                                                                                   \
-    k_cheb_step<T, BB, M, N, D><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, ragged, pr.rowptr.get(),               \
-                                                        pr.colidx.get(), Sv, y, r, yio, skip, it, a, b, partial, dpart, dot_mode == 2)
-#define GSC_CHEB(BB, M, N) \
-    if (dot_mode) GSC_CHEB_D(BB, M, N, 2); else if (partial) GSC_CHEB_D(BB, M, N, 1); else GSC_CHEB_D(BB, M, N, 0);
-#define GSC_CHEB_N(BB, M) \
-    if (td.nt) { GSC_CHEB(BB, M, true) } else { GSC_CHEB(BB, M, false) }
+#define GSC_CHEB_D(BB, SP, M, N, D)                                                                               \
+    k_cheb_step<T, BB, SP, M, N, D><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, ragged, pr.rowptr.get(),          \
+                                                            pr.colidx.get(), Sv, y, r, yio, skip, it, a, b,       \
+                                                            partial, dpart, dot_mode == 2)
+#define GSC_CHEB(BB, SP, M, N)                      \
+    if (dot_mode) GSC_CHEB_D(BB, SP, M, N, 2);      \
+    else if (partial) GSC_CHEB_D(BB, SP, M, N, 1);  \
+    else GSC_CHEB_D(BB, SP, M, N, 0);
+#define GSC_CHEB_N(BB, SP, M) \
+    if (td.nt) { GSC_CHEB(BB, SP, M, true) } else { GSC_CHEB(BB, SP, M, false) }
+#define GSC_CHEB_M(BB, SP)                    \
+    if (mode == 0) { GSC_CHEB_N(BB, SP, 0) }  \
+    else if (mode == 1) { GSC_CHEB_N(BB, SP, 1) } else { GSC_CHEB_N(BB, SP, 2) }
 #define GSC_CHEB_B(BB) \
-    if (mode == 0) { GSC_CHEB_N(BB, 0) } else if (mode == 1) { GSC_CHEB_N(BB, 1) } else { GSC_CHEB_N(BB, 2) }
+    if (waves == 1) { GSC_CHEB_M(BB, 1) } else { GSC_CHEB_M(BB, kSplit<T>) }
     if (pr.B == 4) { GSC_CHEB_B(4) } else { GSC_CHEB_B(6) }
 #undef GSC_CHEB_B
+#undef GSC_CHEB_M
 #undef GSC_CHEB_N
 #undef GSC_CHEB
 #undef GSC_CHEB_D
@@ -286,14 +293,14 @@ template <> struct mx_lane<c64x2> {
     static __device__ c64 &at(c64x2 &v, int h) { return h ? v.b : v.a; }
 };
 
-template <typename V, int B, int MODE, int FIN, int OUT>
+template <typename V, int B, int SPLIT, int MODE, int FIN, int OUT>
 __global__ __launch_bounds__(kBlock) void k_cheb_mx(
     int nb, int Rp, int col0, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const float *__restrict__ Sv, const c64 *__restrict__ y, const c64 *__restrict__ f, c64 *__restrict__ yio,
     c128 *__restrict__ Y, const c128 *__restrict__ r, const int *__restrict__ skip, float inv_theta, float c1,
     float c2, double *__restrict__ partial, c128 *__restrict__ dpart, int dot_active_only) {
     using L = mx_lane<V>;
-    constexpr int W = L::W, SPLIT = kWavesPerBlock;
+    constexpr int W = L::W;
     __shared__ RowSums<V, B, SPLIT> red;
     int cx, g;
     xcd_remap_chunks(ragged, cx, g);
@@ -369,13 +376,12 @@ __global__ __launch_bounds__(kBlock) void k_cheb_mx(
 
 // f = r - S Y in FP64 (S, Y, r in FP64), stored in complex64 as the
 // right-hand side of the next complex64 round.
-template <int B>
+template <int B, int SPLIT>
 __global__ __launch_bounds__(kBlock) void k_mx_resid(
     int nb, int Rp, int col0, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const double *__restrict__ Sv, const c128 *__restrict__ Y, const c128 *__restrict__ r, c64 *__restrict__ f,
     const int *__restrict__ skip) {
     using V = c128;
-    constexpr int SPLIT = kWavesPerBlock;
     __shared__ RowSums<V, B, SPLIT> red;
     int cx, g;
     xcd_remap_chunks(ragged, cx, g);
@@ -401,34 +407,36 @@ void launch_cheb_mx(hipStream_t st, const Pair &pr, const TileDims &td, int mode
     GSC_REQUIRE(fin == 0 || Y != nullptr, "a final step needs the FP64 solution");
     GSC_REQUIRE(fin != 0 || partial == nullptr, "only a final step leaves partial sums");
     const float it = static_cast<float>(inv_theta), a = static_cast<float>(c1), b = static_cast<float>(c2);
-    const int G = partial ? td.Gs : td.Gw;
     // 128-column pieces with two columns per lane, a 64-column tail with one
     const int n2 = ncols / 128 * 128;
-#define GSC_MX(V, BB, M, F, O)                                                                                    \
-    k_cheb_mx<V, BB, M, F, O><<<grid, kBlock, 0, st>>>(td.nb, td.Rp, c0, ragged, pr.rowptr.get(),                 \
-                                                       pr.colidx.get(), Sv, y, f, yio, Y, r, skip, it, a, b, partial, dpart, dot_active_only)
-#define GSC_MX_O(V, BB, M, F) \
-    if (dot) GSC_MX(V, BB, M, F, 2); else if (partial) GSC_MX(V, BB, M, F, 1); else GSC_MX(V, BB, M, F, 0);
-#define GSC_MX_F(V, BB, M)                   \
-    if (fin == 0) { GSC_MX(V, BB, M, 0, 0); } \
-    else if (fin == 1) { GSC_MX_O(V, BB, M, 1) } else { GSC_MX_O(V, BB, M, 2) }
-#define GSC_MX_M(V, BB) \
-    if (mode == 0) { GSC_MX_F(V, BB, 0) } else if (mode == 1) { GSC_MX_F(V, BB, 1) } else { GSC_MX_F(V, BB, 2) }
-#define GSC_MX_B(V) \
-    if (pr.B == 4) { GSC_MX_M(V, 4) } else { GSC_MX_M(V, 6) }
+#define GSC_MX(V, BB, SP, M, F, O)                                                                          \
+    k_cheb_mx<V, BB, SP, M, F, O><<<grid, kBlock, 0, st>>>(td.nb, td.Rp, c0, ragged, pr.rowptr.get(),       \
+                                                           pr.colidx.get(), Sv, y, f, yio, Y, r, skip, it,  \
+                                                           a, b, partial, dpart, dot_active_only)
+#define GSC_MX_O(V, BB, SP, M, F)                     \
+    if (dot) GSC_MX(V, BB, SP, M, F, 2);              \
+    else if (partial) GSC_MX(V, BB, SP, M, F, 1);     \
+    else GSC_MX(V, BB, SP, M, F, 0);
+#define GSC_MX_F(V, BB, SP, M)                   \
+    if (fin == 0) { GSC_MX(V, BB, SP, M, 0, 0); } \
+    else if (fin == 1) { GSC_MX_O(V, BB, SP, M, 1) } else { GSC_MX_O(V, BB, SP, M, 2) }
+#define GSC_MX_M(V, BB, SP)                    \
+    if (mode == 0) { GSC_MX_F(V, BB, SP, 0) }  \
+    else if (mode == 1) { GSC_MX_F(V, BB, SP, 1) } else { GSC_MX_F(V, BB, SP, 2) }
     if (n2 > 0) {
-        const dim3 grid(n2 / 128, G);
+        const dim3 grid(n2 / 128, partial ? td.Gs : td.Gw);
         const int c0 = col0;
         const bool ragged = ragged_end(c0 + n2, td.R, 128);
-        GSC_MX_B(c64x2)
+        if (pr.B == 4) { GSC_MX_M(c64x2, 4, 4) } else { GSC_MX_M(c64x2, 6, 4) }
     }
     if (n2 < ncols) {
-        const dim3 grid((ncols - n2) / 64, G);
+        const int waves = step_waves(td.nb, 1, td.row_orbitals, true);
+        const dim3 grid(1, partial ? td.Gs : waves == 1 ? td.G1 : td.Gw);
         const int c0 = col0 + n2;
-        const bool ragged = ragged_end(col0 + ncols, td.R, 64);
-        GSC_MX_B(c64)
+        const bool ragged = false;      // one chunk
+        if (pr.B == 4) { if (waves == 1) { GSC_MX_M(c64, 4, 1) } else { GSC_MX_M(c64, 4, 4) } }
+        else { if (waves == 1) { GSC_MX_M(c64, 6, 1) } else { GSC_MX_M(c64, 6, 4) } }
     }
-#undef GSC_MX_B
 #undef GSC_MX_M
 #undef GSC_MX_F
 #undef GSC_MX_O
@@ -440,62 +448,36 @@ void launch_mx_resid(hipStream_t st, const Pair &pr, const TileDims &td, int col
                      const c128 *Y, const c128 *r, c64 *f, const int *skip) {
     GSC_REQUIRE(col0 % 64 == 0 && ncols % 64 == 0 && ncols > 0 && col0 + ncols <= td.Rp,
                 "Chebyshev column block outside the tile");
-    dim3 grid(ncols / 64, td.Gw), block(kBlock);
+    const int waves = step_waves(td.nb, ncols / 64, td.row_orbitals, false);
+    dim3 grid(ncols / 64, waves == 1 ? td.G1 : td.Gw), block(kBlock);
     const bool ragged = ragged_end(col0 + ncols, td.R, 64);
-    if (pr.B == 4)
-        k_mx_resid<4><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, ragged, pr.rowptr.get(), pr.colidx.get(), Sv, Y, r, f,
-                                              skip);
-    else
-        k_mx_resid<6><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, ragged, pr.rowptr.get(), pr.colidx.get(), Sv, Y, r, f,
-                                              skip);
+#define GSC_RESID(BB, SP)                                                                                       \
+    k_mx_resid<BB, SP><<<grid, block, 0, st>>>(td.nb, td.Rp, col0, ragged, pr.rowptr.get(), pr.colidx.get(), Sv, \
+                                               Y, r, f, skip)
+    if (pr.B == 4) { if (waves == 1) GSC_RESID(4, 1); else GSC_RESID(4, 4); }
+    else { if (waves == 1) GSC_RESID(6, 1); else GSC_RESID(6, 4); }
+#undef GSC_RESID
     GSC_HIP(hipGetLastError());
 }
 
 // ------------------------------------------------------------------ launchers
-// Row groups of the product kernels.  Launches that leave no partial sums give
-// every block row its own workgroup (1, 2, 4 and 8 rows a workgroup on the
-// Chebyshev step: 4,096 Si x 128 columns 35.8 / 38.2 / 40.8 / 35.6 us, 2,668 Si
-// x 128 25.2 / 27.7 / 29.5 / 31.8, 64 H2O x 384 9.5 / 11.9 / 18.7 / 35.5).  Those
-// that do leave them (one launch of about twelve) stay within about 1024
-// groups: the reductions read every group's value of every column.
-void set_spmm_geometry(TileDims &td, bool one_wave) {
-    auto up8 = [](int64_t g) { return static_cast<int>((std::min<int64_t>(g, 65528) + 7) / 8 * 8); };
+void set_spmm_geometry(TileDims &td, const Pair &pr, bool one_wave) {
     const int w = td.cb > 0 && td.cb < td.Rp ? td.cb : td.Rp;   // width of a Chebyshev launch
-    td.G1 = one_wave_groups(td.nb, std::max(1, w / 64));
-    td.Gw = up8(td.nb);
-    const int64_t rows = (td.nb + 1023) / 1024;
-    td.Gs = one_wave ? td.G1 : up8((td.nb + rows - 1) / rows);
-}
-
-// Groups of four block rows (one wave each): one row a wave while a launch
-// stays within 16384 workgroups, else about 4096 workgroups with equal rows
-// per wave, at least 256 groups when there are more than 8 column chunks (an
-// XCD would otherwise run the groups of several chunks at once).
-int one_wave_groups(int64_t nb, int chunks) {
-    const int64_t slots = std::max<int64_t>(1, (nb + 3) / 4);
-    int64_t g = slots;
-    if (chunks * slots > 16384) {
-        int64_t g0 = std::max(1, 4096 / chunks);
-        if (chunks > 8) g0 = std::max<int64_t>(g0, 256);
-        g0 = std::min(g0, slots);
-        const int64_t passes = (slots + g0 - 1) / g0;
-        g = (slots + passes - 1) / passes;
-    }
-    return static_cast<int>((std::min<int64_t>(g, 65528) + 7) / 8 * 8);
+    td.row_orbitals = static_cast<int>(pr.nnzb * pr.B / pr.nb);
+    static_cast<RowGroups &>(td) = row_groups(td.nb, td.Rp / 64, std::max(1, w / 64), one_wave);
 }
 
 template <typename T>
 void launch_spmm_seed(hipStream_t st, const Pair &pr, const TileDims &td, const T *Sv, const T *Hv,
                       const cpx<T> *p, cpx<T> *q, const c128 *z, const int *seed, const int *skip,
                       c128 *partial) {
-    const int split = seed_split<T>(td.nb, td.Rp / 64);
-    dim3 grid(td.Rp / 64, td.Gs), block(kBlock);
+    dim3 grid(td.Rp / 64, td.G2), block(kBlock);
     const bool ragged = ragged_end(td.Rp, td.R, 64);
 #define GSC_SEED(BB, SP)                                                                                         \
     k_spmm_seed<T, BB, SP><<<grid, block, 0, st>>>(td.nb, td.Rp, ragged, pr.rowptr.get(), pr.colidx.get(), Sv, Hv,   \
                                                    p, q, z, seed, skip, partial)
 #define GSC_SEED_S(BB) \
-    if (split == 1) GSC_SEED(BB, 1); else GSC_SEED(BB, kSplit<T>);
+    if (td.waves2 == 1) GSC_SEED(BB, 1); else GSC_SEED(BB, kSplit<T>);
     if (pr.B == 4) { GSC_SEED_S(4) } else { GSC_SEED_S(6) }
 #undef GSC_SEED_S
 #undef GSC_SEED

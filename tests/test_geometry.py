@@ -15,6 +15,14 @@ extern "C" void order(int gx, int G, int ragged, int *cx, int *gy) {
     for (int l = 0; l < gx * G; ++l) chunk_order(l, gx, G, ragged, cx[l], gy[l]);
 }
 extern "C" int ragged(int end, int R, int width) { return ragged_end(end, R, width); }
+extern "C" void groups(int64_t nb, int chunks, int width, int one_wave, int *out) {
+    const RowGroups g = row_groups(nb, chunks, width, one_wave);
+    const int v[5] = {g.Gs, g.Gw, g.G1, g.G2, g.waves2};
+    for (int i = 0; i < 5; ++i) out[i] = v[i];
+}
+extern "C" int step(int64_t nb, int chunks, int64_t row_orbitals, int narrow) {
+    return step_waves(nb, chunks, row_orbitals, narrow);
+}
 """
 
 
@@ -62,3 +70,34 @@ def test_ragged_end(lib):
     """A quarter of the last chunk empty, of 64 and of 128 columns."""
     assert [lib.ragged(192, R, 64) for R in (129, 176, 177, 192, 300)] == [1, 1, 0, 0, 0]
     assert [lib.ragged(256, R, 128) for R in (130, 224, 225, 256)] == [1, 1, 0, 0]
+
+
+@pytest.mark.parametrize("one_wave", [0, 1])
+@pytest.mark.parametrize("chunks,width", [(1, 1), (2, 2), (4, 4), (8, 1), (24, 24)])
+def test_row_groups(lib, chunks, width, one_wave):
+    """Groups that leave partial sums hold at most four rows of one chunk (one a
+    wave) however many rows there are, and one wave a row has no more groups than
+    its rows fill, so that no XCD's share is empty."""
+    for nb in [1, 3, 8, 9, 255, 256, 1023, 1024, 1025, 2048, 2049, 3072, 4096, 4097, 8192, 19038, 32768, 65536]:
+        out = np.empty(5, np.int32)
+        lib.groups(ctypes.c_int64(nb), chunks, width, one_wave, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int)))
+        Gs, Gw, G1, G2, waves2 = out
+        slots = -(-nb // 4)
+        assert (out[:4] % 8 == 0).all() and (out[:4] > 0).all()
+        assert Gw == -(-min(nb, 65528) // 8) * 8
+        if width * slots <= 16384:
+            assert 4 * Gs >= nb and 4 * G1 >= nb and 4 * G2 >= nb
+        assert G1 <= -(-slots // 8) * 8
+        if waves2 == 1:
+            assert G2 == G1
+        if one_wave:
+            assert Gs == G1 and waves2 == 1
+
+
+def test_step_waves(lib):
+    """One wave a row for short rows in launches of one chunk with many rows."""
+    step = lambda nb, chunks, orbitals, narrow: lib.step(ctypes.c_int64(nb), chunks, ctypes.c_int64(orbitals), narrow)  # noqa: E731
+    assert [step(nb, 1, 68, 0) for nb in (4096, 12287, 12288, 32768)] == [4, 4, 1, 1]
+    assert [step(nb, 1, 68, 1) for nb in (4095, 4096, 32768)] == [4, 1, 1]
+    assert step(32768, 2, 68, 0) == step(32768, 2, 68, 1) == 4
+    assert step(32768, 1, 162, 0) == step(32768, 1, 162, 1) == 4
