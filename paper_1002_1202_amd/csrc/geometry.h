@@ -100,11 +100,17 @@ inline bool long_rows(int64_t row_orbitals) { return row_orbitals >= 112; }
 
 // Waves that the products with two matrices (S and H: the seed product, the
 // Lanczos product) give a block row.  Their two sums a lane leave 5 waves on a
-// SIMD against 8, so once there are enough rows to fill the card twice over, one
-// wave a row is ahead (microseconds, one wave / four: 4,096 Si x 256 columns 80 /
-// 88, 4,096 Si x 128 45.9 / 47.8; but 256 H2O x 1536 108 / 83, 3,000 H2O x 128
-// 136 / 89, 24 H2O x 192 20.5 / 9.2).
-inline int product_waves(int64_t nb, int chunks) { return nb * chunks >= 8192 ? 1 : 4; }
+// SIMD against 8, so with short rows and enough of them to fill the card one wave a
+// row is ahead; the chain of loads of a long row is worth sharing at every size.  Runs
+// of 30 to 60 iterations, ms, one wave / four.  Short: 1,024 rows x 320 columns 25.0 /
+// 25.4, 4,096 x 64 21.3 / 21.4, 8,192 x 64 19.1 / 19.4, 4,096 x 256 29.4 / 29.8,
+// 2,048 x 128 20.8 / 20.6, 512 x 512 20.9 / 20.8, 512 x 256 12.9 / 12.5, 512 x 64 9.1
+// / 7.7.  Long: 3,000 H2O x 128 29.3 / 28.6, x 192 43.7 / 40.9, x 256 54.5 / 52.0, x
+// 512 110 / 109, 12,000 H2O x 64 62.5 / 60.2; mixed x 192 39.8 / 37.6, x 256 43.9 /
+// 41.1, 12,000 x 64 51.1 / 48.6.
+inline int product_waves(int64_t nb, int chunks, int64_t row_orbitals) {
+    return !long_rows(row_orbitals) && nb * chunks >= 4096 ? 1 : 4;
+}
 
 // Waves that a launch of Chebyshev steps (or of their residuals) gives a block row;
 // narrow: complex64 with one column a lane.  Four, except for short rows in launches
@@ -133,13 +139,13 @@ inline int step_waves(int64_t nb, int chunks, int64_t row_orbitals, bool narrow)
 // that, 4 / 2 / 1 at 8,192 rows x 128 columns 30.7 / 32.5 / 36.9 ms a run.  One wave
 // a row never takes more groups than that needs: the groups beyond the last row
 // would be whole XCDs' share (2,048 Si x 256 columns, seed product 63 -> 47 us).
-inline RowGroups row_groups(int64_t nb, int chunks, int width, bool one_wave) {
+inline RowGroups row_groups(int64_t nb, int chunks, int width, int64_t row_orbitals, bool one_wave) {
     RowGroups g;
     g.G1 = one_wave_groups(nb, width);
     g.Gw = up8(nb);
     const int64_t rows = std::min<int64_t>(4, (nb + 1023) / 1024);
     g.Gs = one_wave || rows == 4 ? g.G1 : up8((nb + rows - 1) / rows);
-    g.waves2 = one_wave ? 1 : product_waves(nb, chunks);
+    g.waves2 = one_wave ? 1 : product_waves(nb, chunks, row_orbitals);
     g.G2 = g.waves2 == 1 ? g.G1 : g.Gs;
     return g;
 }

@@ -464,7 +464,7 @@ void launch_mx_resid(hipStream_t st, const Pair &pr, const TileDims &td, int col
 void set_spmm_geometry(TileDims &td, const Pair &pr, bool one_wave) {
     const int w = td.cb > 0 && td.cb < td.Rp ? td.cb : td.Rp;   // width of a Chebyshev launch
     td.row_orbitals = static_cast<int>(pr.nnzb * pr.B / pr.nb);
-    static_cast<RowGroups &>(td) = row_groups(td.nb, td.Rp / 64, std::max(1, w / 64), one_wave);
+    static_cast<RowGroups &>(td) = row_groups(td.nb, td.Rp / 64, std::max(1, w / 64), td.row_orbitals, one_wave);
 }
 
 template <typename T>

@@ -15,8 +15,8 @@ extern "C" void order(int gx, int G, int ragged, int *cx, int *gy) {
     for (int l = 0; l < gx * G; ++l) chunk_order(l, gx, G, ragged, cx[l], gy[l]);
 }
 extern "C" int ragged(int end, int R, int width) { return ragged_end(end, R, width); }
-extern "C" void groups(int64_t nb, int chunks, int width, int one_wave, int *out) {
-    const RowGroups g = row_groups(nb, chunks, width, one_wave);
+extern "C" void groups(int64_t nb, int chunks, int width, int64_t row_orbitals, int one_wave, int *out) {
+    const RowGroups g = row_groups(nb, chunks, width, row_orbitals, one_wave);
     const int v[5] = {g.Gs, g.Gw, g.G1, g.G2, g.waves2};
     for (int i = 0; i < 5; ++i) out[i] = v[i];
 }
@@ -72,6 +72,13 @@ def test_ragged_end(lib):
     assert [lib.ragged(256, R, 128) for R in (130, 224, 225, 256)] == [1, 1, 0, 0]
 
 
+def groups(lib, nb, chunks, width, orbitals, one_wave):
+    out = np.empty(5, np.int32)
+    lib.groups(ctypes.c_int64(nb), chunks, width, ctypes.c_int64(orbitals), one_wave,
+               out.ctypes.data_as(ctypes.POINTER(ctypes.c_int)))
+    return out
+
+
 @pytest.mark.parametrize("one_wave", [0, 1])
 @pytest.mark.parametrize("chunks,width", [(1, 1), (2, 2), (4, 4), (8, 1), (24, 24)])
 def test_row_groups(lib, chunks, width, one_wave):
@@ -79,8 +86,7 @@ def test_row_groups(lib, chunks, width, one_wave):
     wave) however many rows there are, and one wave a row has no more groups than
     its rows fill, so that no XCD's share is empty."""
     for nb in [1, 3, 8, 9, 255, 256, 1023, 1024, 1025, 2048, 2049, 3072, 4096, 4097, 8192, 19038, 32768, 65536]:
-        out = np.empty(5, np.int32)
-        lib.groups(ctypes.c_int64(nb), chunks, width, one_wave, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int)))
+        out = groups(lib, nb, chunks, width, 68, one_wave)
         Gs, Gw, G1, G2, waves2 = out
         slots = -(-nb // 4)
         assert (out[:4] % 8 == 0).all() and (out[:4] > 0).all()
@@ -101,3 +107,11 @@ def test_step_waves(lib):
     assert [step(nb, 1, 68, 1) for nb in (4095, 4096, 32768)] == [4, 1, 1]
     assert step(32768, 2, 68, 0) == step(32768, 2, 68, 1) == 4
     assert step(32768, 1, 162, 0) == step(32768, 1, 162, 1) == 4
+
+
+def test_product_waves(lib):
+    """The products with two matrices: one wave a row for short rows when there are
+    enough of them; long rows are shared at every size."""
+    waves = lambda nb, chunks, orbitals: groups(lib, nb, chunks, chunks, orbitals, 0)[4]  # noqa: E731
+    assert [waves(nb, c, 68) for nb, c in ((4095, 1), (4096, 1), (2047, 2), (2048, 2), (32768, 8))] == [4, 1, 4, 1, 1]
+    assert [waves(nb, c, 162) for nb, c in ((3000, 2), (3000, 3), (3000, 8), (12000, 1), (65536, 8))] == [4] * 5
