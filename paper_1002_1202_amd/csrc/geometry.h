@@ -133,17 +133,20 @@ inline int step_waves(int64_t nb, int chunks, int64_t row_orbitals, bool narrow)
 // Chebyshev step: 4,096 Si x 128 columns 35.8 / 38.2 / 40.8 / 35.6 us, 2,668 Si x
 // 128 25.2 / 27.7 / 29.5 / 31.8, 64 H2O x 384 9.5 / 11.9 / 18.7 / 35.5).  Those that
 // leave them take up to four rows a group, as many as bring the groups to about 1024
-// (the reductions read every group's value of every column), and never more: with
-// 1024 groups whatever the rows, a launch of one chunk is too small for the card (N
-// 131,072: seed product 75 -> 115 us a launch of 8 chunks).  Fewer rows a group than
-// that, 4 / 2 / 1 at 8,192 rows x 128 columns 30.7 / 32.5 / 36.9 ms a run.  One wave
-// a row never takes more groups than that needs: the groups beyond the last row
-// would be whole XCDs' share (2,048 Si x 256 columns, seed product 63 -> 47 us).
+// and the workgroups of the tile's chunks to about 1024 (the reductions read every
+// group's value of every column), and never more: with 1024 groups whatever the rows,
+// a launch of one chunk is too small for the card (N 131,072, 60 seed products of 8
+// chunks 115 ms, now 73).  Fewer rows a group than that, 4 / 2 / 1 at 8,192 rows x
+// 128 columns 30.7 / 32.5 / 36.9 ms a run; at 512 rows x 512 columns 19.5 / 20.0 /
+// 20.4, 256 x 1024 21.1 / 21.5 / 22.4, 1,024 x 1024 55.4 / - / 57.1, 256 H2O x 1024
+// 39.4 / 39.9 / 40.7.  One wave a row never takes more groups than that needs: the
+// groups beyond the last row would be whole XCDs' share (2,048 Si x 256 columns, seed
+// product 65 -> 42 us).
 inline RowGroups row_groups(int64_t nb, int chunks, int width, int64_t row_orbitals, bool one_wave) {
     RowGroups g;
     g.G1 = one_wave_groups(nb, width);
     g.Gw = up8(nb);
-    const int64_t rows = std::min<int64_t>(4, (nb + 1023) / 1024);
+    const int64_t rows = std::min<int64_t>(4, std::max((nb + 1023) / 1024, nb * chunks / 1024));
     g.Gs = one_wave || rows == 4 ? g.G1 : up8((nb + rows - 1) / rows);
     g.waves2 = one_wave ? 1 : product_waves(nb, chunks, row_orbitals);
     g.G2 = g.waves2 == 1 ? g.G1 : g.Gs;

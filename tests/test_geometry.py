@@ -96,6 +96,8 @@ def test_row_groups(lib, chunks, width, one_wave):
         assert G1 <= -(-slots // 8) * 8
         if waves2 == 1:
             assert G2 == G1
+        if chunks * nb >= 4096 and not one_wave:
+            assert Gs == G1             # four rows a group
         if one_wave:
             assert Gs == G1 and waves2 == 1
 
