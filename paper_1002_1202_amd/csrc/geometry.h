@@ -153,4 +153,16 @@ inline RowGroups row_groups(int64_t nb, int chunks, int width, int64_t row_orbit
     return g;
 }
 
+// ------------------------------------------------------------------ small systems
+// Whether one workgroup a column (small.hip) also carries the full x^k and p^k of K
+// shifts of N orbitals: their update is one CU's traffic there and the card's on the
+// tiles.  (The projected carries are ahead at every K measured, up to 4096.)  One
+// workgroup | tiles, ms, 8 columns, shifts over the whole spectrum: N 512 K 1024 33 |
+// 41, K 2048 53 | 48, K 4096 92 | 64; N 384 K 2048 38 | 46, K 4096 70 | 60; N 144 K
+// 2048 43 | 57, K 4096 76 | 69.  All shifts inside a band (none finishes early): N
+// 512 K 512 35 | 43, K 1024 56 | 52; N 384 K 1024 39 | 48, K 2048 71 | 61; N 256 K
+// 1024 29 | 47, K 2048 55 | 59; N 144 K 1024 65 | 70, K 2048 124 | 93.  The line
+// lies between the two kinds of grids.
+inline bool small_full_carry(int64_t N, int64_t K) { return K <= 2048 && N * K <= 5 << 17; }
+
 }  // namespace gsc

@@ -33,8 +33,9 @@ struct SmallSolve {
     int *switches;                   // seed switches and restarts, summed over columns
 };
 
-// whether one workgroup a column is the way for R columns of M projections
-bool small_fits(const Pair &pr, int M, int R, int num_cu);
+// whether one workgroup a column is the way for R columns of M projections, or of
+// the full carry of K shifts
+bool small_fits(const Pair &pr, int K, bool full, int M, int R, int num_cu);
 // stored blocks a lane takes of the longest block row
 int small_lane_blocks(const Pair &pr);
 size_t small_packed(const Pair &pr, int nj);

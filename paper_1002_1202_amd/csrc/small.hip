@@ -593,8 +593,8 @@ size_t small_lds(int N, int64_t nnzb, int M) {
 
 }  // namespace
 
-bool small_fits(const Pair &pr, int M, int R, int num_cu) {
-    if (pr.n > kSmallRows) return false;
+bool small_fits(const Pair &pr, int K, bool full, int M, int R, int num_cu) {
+    if (pr.n > kSmallRows || (full && !small_full_carry(pr.n, K))) return false;
     const int N = static_cast<int>(pr.n);
     if (static_cast<int64_t>(N) * div_up(R, num_cu) > kSmallRowRounds) return false;
     return small_lds(N, pr.nnzb, M) <= size_t{64} << 10 && M <= small_threads(N);

@@ -1707,7 +1707,7 @@ template <typename T> class TileSolver {
     // follows all columns), no per-kernel timing (there is one kernel).
     bool small_ok(const gsc_opts &o) const {
         return std::is_same<T, double>::value && cheb_ok_ && !o.inner_relax && !prof_.on &&
-               small_fits(pr_, t_.Mu + t_.srow, t_.td.R, ctx_.num_cu);
+               small_fits(pr_, t_.td.K, full_, t_.Mu + t_.srow, t_.td.R, ctx_.num_cu);
     }
     int run_small(const gsc_opts &o) {
         auto &td = t_.td;

@@ -20,6 +20,7 @@ extern "C" void groups(int64_t nb, int chunks, int width, int64_t row_orbitals, 
     const int v[5] = {g.Gs, g.Gw, g.G1, g.G2, g.waves2};
     for (int i = 0; i < 5; ++i) out[i] = v[i];
 }
+extern "C" int small_full(int64_t N, int64_t K) { return small_full_carry(N, K); }
 extern "C" int step(int64_t nb, int chunks, int64_t row_orbitals, int narrow) {
     return step_waves(nb, chunks, row_orbitals, narrow);
 }
@@ -117,3 +118,10 @@ def test_product_waves(lib):
     waves = lambda nb, chunks, orbitals: groups(lib, nb, chunks, chunks, orbitals, 0)[4]  # noqa: E731
     assert [waves(nb, c, 68) for nb, c in ((4095, 1), (4096, 1), (2047, 2), (2048, 2), (32768, 8))] == [4, 1, 4, 1, 1]
     assert [waves(nb, c, 162) for nb, c in ((3000, 2), (3000, 3), (3000, 8), (12000, 1), (65536, 8))] == [4] * 5
+
+
+def test_small_full_carry(lib):
+    """Many shifts of the full carry go to the tiles."""
+    fits = lambda N, K: lib.small_full(ctypes.c_int64(N), ctypes.c_int64(K))  # noqa: E731
+    assert [fits(N, K) for N, K in ((512, 1280), (320, 2048), (4, 2048), (512, 64))] == [1] * 4
+    assert [fits(N, K) for N, K in ((512, 1281), (321, 2048), (4, 2049), (384, 4096), (512, 65535))] == [0] * 5
