@@ -108,7 +108,8 @@ typedef struct {
                               gsc_stats.res_true (full carry only: the
                               projected carry keeps no x_k to check)          */
     int spmm_kernel;       /* [0 = auto = 1] product kernel layout: 1 one block
-                              row x 64 rhs per workgroup of four waves (the
+                              row x 64 rhs per workgroup of four waves, or
+                              per wave in launches of many short rows (the
                               complex64 steps of GSC_MIXED: 128 rhs, two per
                               lane)                                           */
     int inner_method;      /* [0 = auto] inner solver for S r' = r: 1 CG (the
@@ -154,11 +155,14 @@ typedef struct {
                               of finished jobs are released when a starting
                               job needs their room (else at the end).  auto =
                               80 % of the device memory free at the call.    */
-    int row_groups;        /* [0 = auto] workgroup rows of the product and
-                              Chebyshev launches (a multiple of 8, at most
-                              65528; capped at one block row per workgroup);
-                              auto: one block row per workgroup, and about
-                              1024 for the launches that leave partial sums   */
+    int row_groups;        /* [0 = auto] groups of four block rows of the product
+                              and Chebyshev launches (a multiple of 8, at most
+                              65528; capped at a group for every four rows): a
+                              workgroup each, or four workgroups of one row
+                              each in launches that share rows and leave no
+                              partial sums; auto: every row in flight, fewer
+                              groups where a launch would exceed 16384
+                              workgroups                                      */
     int reserved[1];
 } gsc_opts;
 

@@ -121,9 +121,14 @@ def _store(cache):
         pass
 
 
+# Part of every cache key: raised when the kernels behind an option's values change,
+# so that picks timed on other kernels are not replayed (1: keys without it).
+GEOMETRY = 2
+
+
 def shape_key(block, n, nrhs, nshift, precision, carry, tag="solve"):
     b2 = lambda v: int(round(math.log2(max(v, 1))))  # noqa: E731
-    return f"{tag}|gfx950|B{block}|N2^{b2(n)}|R2^{b2(nrhs)}|K2^{b2(nshift)}|{precision}|{carry}"
+    return f"{tag}|gfx950|B{block}|N2^{b2(n)}|R2^{b2(nrhs)}|K2^{b2(nshift)}|{precision}|{carry}|g{GEOMETRY}"
 
 
 def _wall(fn, reps=2):
@@ -195,7 +200,7 @@ def batch_key(problems, precision):
     tot = sum(p["pair"].n * len(p["rhs"]) for p in problems)
     b2 = lambda v: int(round(math.log2(max(v, 1))))  # noqa: E731
     return (f"batched|gfx950|Nmax2^{b2(nmax)}|NR2^{b2(tot)}|S2^{b2(len(problems))}"
-            f"|K2^{b2(max(len(p['z']) for p in problems))}|{precision}|projected")
+            f"|K2^{b2(max(len(p['z']) for p in problems))}|{precision}|projected|g{GEOMETRY}")
 
 
 def tune_batched(ctx, problems, precision="mixed", tol=1e-6, t1=8, t2=24, candidates=None, space=None,

@@ -153,6 +153,15 @@ inline RowGroups row_groups(int64_t nb, int chunks, int width, int64_t row_orbit
     return g;
 }
 
+// The same with a caller's number of groups (gsc_opts.row_groups), each of four block
+// rows as in the automatic rule beyond 3,072 rows: launches that share rows without
+// partial sums take four workgroups for one group, so that as many rows are in flight.
+inline void set_groups(RowGroups &g, int64_t nb, int asked) {
+    const int64_t slots = (nb + 3) / 4;
+    g.Gs = g.G1 = g.G2 = up8(std::min<int64_t>(asked, slots));
+    g.Gw = up8(std::min<int64_t>(4 * static_cast<int64_t>(asked), nb));
+}
+
 // ------------------------------------------------------------------ small systems
 // Whether one workgroup a column (small.hip) also carries the full x^k and p^k of K
 // shifts of N orbitals: their update is one CU's traffic there and the card's on the

@@ -1447,12 +1447,7 @@ template <typename T> class TileSolver {
             if (huge) cb = 64;
             td.cb = (cb >= 64 && cb < Rp) ? cb : Rp;
             set_spmm_geometry(td, pr_, kSplit<T> == 1);
-            if (req.opts.row_groups > 0) {
-                // caller's row groups, at most one block row a workgroup (a
-                // wave in the all-complex64 process)
-                const int cap = kSplit<T> == 1 ? (td.nb + 3) / 4 : td.nb;
-                td.Gs = td.Gw = td.G1 = td.G2 = (std::min(req.opts.row_groups, cap) + 7) / 8 * 8;
-            }
+            if (req.opts.row_groups > 0) set_groups(td, td.nb, req.opts.row_groups);
             td.nt = req.opts.stream_hint == 2 || (req.opts.stream_hint == 0 && huge);
         }
         st_ = ctx_.stream;

@@ -20,6 +20,12 @@ extern "C" void groups(int64_t nb, int chunks, int width, int64_t row_orbitals, 
     const int v[5] = {g.Gs, g.Gw, g.G1, g.G2, g.waves2};
     for (int i = 0; i < 5; ++i) out[i] = v[i];
 }
+extern "C" void asked(int64_t nb, int chunks, int groups, int *out) {
+    RowGroups g = row_groups(nb, chunks, chunks, 68, false);
+    set_groups(g, nb, groups);
+    const int v[5] = {g.Gs, g.Gw, g.G1, g.G2, g.waves2};
+    for (int i = 0; i < 5; ++i) out[i] = v[i];
+}
 extern "C" int small_full(int64_t N, int64_t K) { return small_full_carry(N, K); }
 extern "C" int step(int64_t nb, int chunks, int64_t row_orbitals, int narrow) {
     return step_waves(nb, chunks, row_orbitals, narrow);
@@ -125,3 +131,19 @@ def test_small_full_carry(lib):
     fits = lambda N, K: lib.small_full(ctypes.c_int64(N), ctypes.c_int64(K))  # noqa: E731
     assert [fits(N, K) for N, K in ((512, 1280), (320, 2048), (4, 2048), (512, 64))] == [1] * 4
     assert [fits(N, K) for N, K in ((512, 1281), (321, 2048), (4, 2049), (384, 4096), (512, 65535))] == [0] * 5
+
+
+def test_asked_row_groups(lib):
+    """A caller's groups hold four rows in flight each, shared rows or not, and no
+    group lies beyond the last row."""
+    def asked(nb, g):
+        out = np.empty(5, np.int32)
+        lib.asked(ctypes.c_int64(nb), 2, g, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int)))
+        return out.tolist()
+    assert asked(32768, 1024)[:4] == [1024, 4096, 1024, 1024]
+    assert asked(4096, 1024)[:4] == [1024, 4096, 1024, 1024]
+    assert asked(4096, 65528)[:4] == [1024, 4096, 1024, 1024]
+    assert asked(19038, 8)[:4] == [8, 32, 8, 8]
+    assert asked(72, 64)[:4] == [24, 72, 24, 24]
+    assert asked(100000, 65528)[:4] == [25000, 65528, 25000, 25000]
+    assert asked(1, 8)[:4] == [8, 8, 8, 8]
