@@ -32,8 +32,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 # sources whose change invalidates a traffic summary of a product kernel
 KERNEL_SOURCES = {
-    "cheb_step": ["csrc/spmm.hip", "csrc/spmm.h", "csrc/kernels.h"],
-    "cheb_mx": ["csrc/spmm.hip", "csrc/spmm.h", "csrc/kernels.h"],
+    "cheb_step": ["csrc/spmm.hip", "csrc/spmm.h", "csrc/kernels.h", "csrc/geometry.h"],
+    "cheb_mx": ["csrc/spmm.hip", "csrc/spmm.h", "csrc/kernels.h", "csrc/geometry.h"],
     "shift_update": ["csrc/solver.hip", "csrc/kernels.h"],
 }
 
