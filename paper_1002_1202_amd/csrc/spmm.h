@@ -129,14 +129,22 @@ __device__ inline V total_sum(V mine, const RowSums<V, B, SPLIT> &red, int a, in
 // row = I B + a.  load fetches what the orbital needs beside the product; with
 // a shared row it is on its way while the row is walked.  combine(acc, acc2)
 // runs on the wave's sums before they are shared; acc2 is shared too when
-// SECOND.  Waves of finished columns (act false) skip the walk, and the loads of
-// single ones are masked off (their lines are not fetched).
+// SECOND.  Waves of finished columns (act false) skip the walk.  Beside columns at
+// work, the lane of a finished one (or of one beyond the last) walks with the first
+// that works: its own lines are not fetched, and its sums are dropped.  Masked off
+// instead, it makes the wave slow: with 8 lanes or fewer at work the walk took up to
+// twice the time of one with all (4,096 Si x 8 columns, truncated runs, masked | not:
+// mixed 13.0 | 10.2 ms, FP64 10.4 | 9.2; x 130 mixed 25.5 | 22.9; 3,000 H2O x 8 18.8 |
+// 14.4).  A branch round the loads alone costs all lanes the loads of several
+// blocks at a time (3,000 H2O x 64 17.6 -> 22.2).
 template <int SPLIT, bool TWO, bool SECOND, typename V, int B, typename Load, typename Combine, typename Done>
 __device__ inline void walk_rows(bool act, int nb, int g, int w, int lane, const int32_t *rowptr,
                                  const int32_t *colidx, const scalar_t<V> *M, const scalar_t<V> *M2, const V *base,
                                  size_t ld, RowSums<V, B, SPLIT> &red, RowSums<V, B, SPLIT> &red2, Load load,
                                  Combine combine, Done done) {
-    if (SPLIT == 1 ? !act : __ballot(act) == 0) return;
+    const unsigned long long on = __ballot(act);
+    if (on == 0) return;
+    const int from = act ? lane : __builtin_ctzll(on);
     constexpr int kOwn = (B + SPLIT - 1) / SPLIT;
     const int q = w % SPLIT, step = kWavesPerBlock / SPLIT * static_cast<int>(gridDim.y);
     for (int I = kWavesPerBlock / SPLIT * g + w / SPLIT; I < nb; I += step) {
@@ -149,24 +157,24 @@ __device__ inline void walk_rows(bool act, int nb, int g, int w, int lane, const
         const size_t row = static_cast<size_t>(I) * B;
         using Extra = decltype(load(row));
         Extra ex[kOwn];
-        if (act) {
-            if constexpr (SPLIT > 1) {
+        if (SPLIT > 1 && act) {
 #pragma unroll
-                for (int o = 0; o < kOwn; ++o)
-                    if (B % SPLIT == 0 || q + o * SPLIT < B) ex[o] = load(row + q + o * SPLIT);
-            }
-            row_blocks<V, B, (SPLIT > 1), TWO>(acc, acc2, b0 + lo, hi - lo, colidx, M, M2, base, ld, lane);
-            combine(acc, acc2);
-            if constexpr (SPLIT == 1) {
+            for (int o = 0; o < kOwn; ++o)
+                if (B % SPLIT == 0 || q + o * SPLIT < B) ex[o] = load(row + q + o * SPLIT);
+        }
+        row_blocks<V, B, (SPLIT > 1), TWO>(acc, acc2, b0 + lo, hi - lo, colidx, M, M2, base, ld, from);
+        combine(acc, acc2);
+        if constexpr (SPLIT == 1) {
+            if (act) {
 #pragma unroll
                 for (int a = 0; a < B; ++a) done(row + a, acc[a], acc2[a], load(row + a));
-            } else {
+            }
+        } else {
 #pragma unroll
-                for (int a = 0; a < B; ++a) {
-                    if (a % SPLIT == q) continue;
-                    red.v[w][a][lane] = acc[a];
-                    if constexpr (SECOND) red2.v[w][a][lane] = acc2[a];
-                }
+            for (int a = 0; a < B; ++a) {
+                if (a % SPLIT == q) continue;
+                red.v[w][a][lane] = acc[a];
+                if constexpr (SECOND) red2.v[w][a][lane] = acc2[a];
             }
         }
         if constexpr (SPLIT > 1) {
