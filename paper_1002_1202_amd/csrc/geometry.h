@@ -89,7 +89,7 @@ struct RowGroups {
     int Gs;       // launches with one matrix that leave partial sums per group and column
     int Gw;       // launches that leave none and share a row
     int G1;       // launches that leave none, one wave a row
-    int G2;       // launches with two matrices (the seed and Lanczos products), with partial sums
+    int G2;       // whole products with partial sums (of the seed, of Lanczos, of the inner CG)
     int waves2;   // waves they give a row, four or one
 };
 
@@ -98,16 +98,18 @@ struct RowGroups {
 // of 6); the line lies between.
 inline bool long_rows(int64_t row_orbitals) { return row_orbitals >= 112; }
 
-// Waves that the products with two matrices (S and H: the seed product, the
-// Lanczos product) give a block row.  Their two sums a lane leave 5 waves on a
-// SIMD against 8, so with short rows and enough of them to fill the card one wave a
-// row is ahead; the chain of loads of a long row is worth sharing at every size.  Runs
-// of 30 to 60 iterations, ms, one wave / four.  Short: 1,024 rows x 320 columns 25.0 /
-// 25.4, 4,096 x 64 21.3 / 21.4, 8,192 x 64 19.1 / 19.4, 4,096 x 256 29.4 / 29.8,
-// 2,048 x 128 20.8 / 20.6, 512 x 512 20.9 / 20.8, 512 x 256 12.9 / 12.5, 512 x 64 9.1
-// / 7.7.  Long: 3,000 H2O x 128 29.3 / 28.6, x 192 43.7 / 40.9, x 256 54.5 / 52.0, x
-// 512 110 / 109, 12,000 H2O x 64 62.5 / 60.2; mixed x 192 39.8 / 37.6, x 256 43.9 /
-// 41.1, 12,000 x 64 51.1 / 48.6.
+// Waves that the whole products with partial sums (S and H: the seed product, the
+// Lanczos product; S: the inner CG) give a block row.  Their groups take up to four
+// rows in turn, and the two sums a lane of S and H leave 5 waves on a SIMD against 8,
+// so with short rows and enough of them to fill the card one wave a row is ahead; the
+// chain of loads of a long row is worth sharing at every size.  Runs of 30 to 60
+// iterations, ms, one wave / four.  Short: 1,024 rows x 320 columns 25.0 / 25.4, 4,096
+// x 64 21.3 / 21.4, 8,192 x 64 19.1 / 19.4, 4,096 x 256 29.4 / 29.8, 2,048 x 128 20.8 /
+// 20.6, 512 x 512 20.9 / 20.8, 512 x 256 12.9 / 12.5, 512 x 64 9.1 / 7.7.  Long: 3,000
+// H2O x 128 29.3 / 28.6, x 192 43.7 / 40.9, x 256 54.5 / 52.0, x 512 110 / 109, 12,000
+// H2O x 64 62.5 / 60.2; mixed x 192 39.8 / 37.6, x 256 43.9 / 41.1, 12,000 x 64 51.1 /
+// 48.6.  Inner CG, 10 iterations, short rows: 18,432 x 190 columns 185 / 191, 18,432 x
+// 64 59.0 / 60.6, 4,096 x 64 9.6 / 9.8, 4,096 x 256 22.3 / 23.1.
 inline int product_waves(int64_t nb, int chunks, int64_t row_orbitals) {
     return !long_rows(row_orbitals) && nb * chunks >= 4096 ? 1 : 4;
 }

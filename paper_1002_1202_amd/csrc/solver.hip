@@ -2304,7 +2304,7 @@ template <typename T> class TileSolver {
                 prof_.begin(st_, KP_SPMM_S, mat_bytes() + 2 * vec);
                 launch_spmm_S<T>(st_, pr_, td, Sv, t_.d.get(), t_.w.get(), t_.c_inner_done.get(), t_.part_d.get());
                 prof_.end(st_);
-                k_cg_a<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.Gs, t_.part_d.get(), cs);
+                k_cg_a<<<td.Rp, kBlock, 0, st_>>>(td.Rp, td.G2, t_.part_d.get(), cs);
                 prof_.begin(st_, KP_CG_UPDATE, 6 * vec);
                 k_cg_update<T><<<eg, eb, 0, st_>>>(td.N, td.Rp, td.Lr, t_.c_inner_done.get(), t_.c_cg_first.get(),
                                                   t_.c_cg_a.get(), t_.d.get(), t_.w.get(), y, t_.res.get(),

@@ -140,13 +140,12 @@ void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors
 
 // w = S d for the columns whose inner solve is still running, plus the
 // per-column partial  Re(d^H S d)  (the CG curvature; S real symmetric).
-template <typename T, int B>
+template <typename T, int B, int SPLIT>
 __global__ __launch_bounds__(kBlock) void k_spmm_S(
     int nb, int Rp, bool ragged, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
     const T *__restrict__ Sv, const cpx<T> *__restrict__ d, cpx<T> *__restrict__ wout,
     const int *__restrict__ skip, double *__restrict__ partial) {
     using V = cpx<T>;
-    constexpr int SPLIT = kSplit<T>;
     __shared__ RowSums<V, B, SPLIT> red;
     __shared__ double redd[kWavesPerBlock][64];
     int cx, g;
@@ -487,14 +486,14 @@ void launch_spmm_seed(hipStream_t st, const Pair &pr, const TileDims &td, const 
 template <typename T>
 void launch_spmm_S(hipStream_t st, const Pair &pr, const TileDims &td, const T *Sv, const cpx<T> *d,
                    cpx<T> *w, const int *skip, double *partial) {
-    dim3 grid(td.Rp / 64, td.Gs), block(kBlock);
+    dim3 grid(td.Rp / 64, td.G2), block(kBlock);
     const bool ragged = ragged_end(td.Rp, td.R, 64);
-    if (pr.B == 4)
-        k_spmm_S<T, 4><<<grid, block, 0, st>>>(td.nb, td.Rp, ragged, pr.rowptr.get(), pr.colidx.get(), Sv,
-                                               d, w, skip, partial);
-    else
-        k_spmm_S<T, 6><<<grid, block, 0, st>>>(td.nb, td.Rp, ragged, pr.rowptr.get(), pr.colidx.get(), Sv,
-                                               d, w, skip, partial);
+#define GSC_S(BB, SP)                                                                                            \
+    k_spmm_S<T, BB, SP><<<grid, block, 0, st>>>(td.nb, td.Rp, ragged, pr.rowptr.get(), pr.colidx.get(), Sv, d, w, \
+                                                skip, partial)
+    if (pr.B == 4) { if (td.waves2 == 1) GSC_S(4, 1); else GSC_S(4, kSplit<T>); }
+    else { if (td.waves2 == 1) GSC_S(6, 1); else GSC_S(6, kSplit<T>); }
+#undef GSC_S
     GSC_HIP(hipGetLastError());
 }
 
