@@ -68,7 +68,10 @@ template <typename V, int B> __device__ inline void mac_block(V (&acc)[B], const
 // exception (AHEAD): scalar loads end together, so an index waits for M's values
 // of its block, and the x loads for both (whole solves without and with it: 256
 // H2O x 1536 360 -> 340 ms, 3,000 H2O x 96 mixed 892 -> 847, 4,096 Si x 256 745 ->
-// 741).  It reads one index past the row, which the pattern's array has room for.
+// 741; one wave a row of 27 blocks, complex64 throughout: 3,000 H2O x 64 9.0 -> 8.0, 256
+// H2O x 1300 13.7 -> 12.8).  It reads one index past the row, which the pattern's array
+// has room for.  Short rows of one wave load the x of two blocks together instead
+// (18,432 Si x 190 mixed 200 | 202 with the index ahead).
 template <typename V, int B, bool AHEAD, bool TWO>
 __device__ inline void row_blocks(V (&acc)[B], V (&acc2)[B], int s0, int n, const int32_t *colidx,
                                   const scalar_t<V> *M, const scalar_t<V> *M2, const V *base, size_t ld, int lane) {
@@ -126,8 +129,11 @@ __device__ inline V total_sum(V mine, const RowSums<V, B, SPLIT> &red, int a, in
 
 // Walks the block rows of row group g: wave w takes its part of each, and for
 // every orbital it finishes calls done(row, (M x)_row, (M2 x)_row, load(row)),
-// row = I B + a.  load fetches what the orbital needs beside the product; with
-// a shared row it is on its way while the row is walked.  combine(acc, acc2)
+// row = I B + a.  load fetches what the orbital needs beside the product: of a
+// shared row, and where it is more than one FP64 value (the Chebyshev step), while the
+// row is walked (18,432 Si x 190 columns FP64, loads one by one between the stores |
+// together after the walk | before it 252 | 249 | 244 ms), else all after it (mixed
+// 200 | 200 | 201).  combine(acc, acc2)
 // runs on the wave's sums before they are shared; acc2 is shared too when
 // SECOND.  Waves of finished columns (act false) skip the walk.  Beside columns at
 // work, the lane of a finished one (or of one beyond the last) walks with the first
@@ -157,17 +163,22 @@ __device__ inline void walk_rows(bool act, int nb, int g, int w, int lane, const
         const size_t row = static_cast<size_t>(I) * B;
         using Extra = decltype(load(row));
         Extra ex[kOwn];
-        if (SPLIT > 1 && act) {
+        constexpr bool kFirst = SPLIT > 1 || (sizeof(V) == 16 && sizeof(Extra) > 16);
+        if (kFirst && act) {
 #pragma unroll
             for (int o = 0; o < kOwn; ++o)
                 if (B % SPLIT == 0 || q + o * SPLIT < B) ex[o] = load(row + q + o * SPLIT);
         }
-        row_blocks<V, B, (SPLIT > 1), TWO>(acc, acc2, b0 + lo, hi - lo, colidx, M, M2, base, ld, from);
+        row_blocks<V, B, (SPLIT > 1 || B == 6), TWO>(acc, acc2, b0 + lo, hi - lo, colidx, M, M2, base, ld, from);
         combine(acc, acc2);
         if constexpr (SPLIT == 1) {
             if (act) {
+                if constexpr (!kFirst) {
 #pragma unroll
-                for (int a = 0; a < B; ++a) done(row + a, acc[a], acc2[a], load(row + a));
+                    for (int a = 0; a < B; ++a) ex[a] = load(row + a);
+                }
+#pragma unroll
+                for (int a = 0; a < B; ++a) done(row + a, acc[a], acc2[a], ex[a]);
             }
         } else {
 #pragma unroll
