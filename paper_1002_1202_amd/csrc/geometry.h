@@ -99,32 +99,31 @@ struct RowGroups {
 inline bool long_rows(int64_t row_orbitals) { return row_orbitals >= 112; }
 
 // Waves that the whole products with partial sums (S and H: the seed product, the
-// Lanczos product; S: the inner CG) give a block row.  Their groups take up to four
-// rows in turn, and the two sums a lane of S and H leave 5 waves on a SIMD against 8,
-// so with short rows and enough of them to fill the card one wave a row is ahead; the
-// chain of loads of a long row is worth sharing at every size.  Runs of 30 to 60
-// iterations, ms, one wave / four.  Short: 1,024 rows x 320 columns 25.0 / 25.4, 4,096
-// x 64 21.3 / 21.4, 8,192 x 64 19.1 / 19.4, 4,096 x 256 29.4 / 29.8, 2,048 x 128 20.8 /
-// 20.6, 512 x 512 20.9 / 20.8, 512 x 256 12.9 / 12.5, 512 x 64 9.1 / 7.7.  Long: 3,000
-// H2O x 128 29.3 / 28.6, x 192 43.7 / 40.9, x 256 54.5 / 52.0, x 512 110 / 109, 12,000
-// H2O x 64 62.5 / 60.2; mixed x 192 39.8 / 37.6, x 256 43.9 / 41.1, 12,000 x 64 51.1 /
-// 48.6.  Inner CG, 10 iterations, short rows: 18,432 x 190 columns 185 / 191, 18,432 x
-// 64 59.0 / 60.6, 4,096 x 64 9.6 / 9.8, 4,096 x 256 22.3 / 23.1.
+// Lanczos product; S: the inner CG) give a block row. Their groups take up to four rows
+// in turn, and the two sums a lane of S and H leave 5 waves on a SIMD against 8, so
+// with short rows and enough of them to fill the card one wave a row is ahead; the
+// chain of loads of a long row is worth sharing at every size. Runs of 30 iterations,
+// ms, one wave / four. Short: 512 rows x 512 columns 11.1 / 11.3, 1,024 x 320 13.5 /
+// 13.7, 2,048 x 128 11.4 / 11.5, 4,096 x 64 11.8 / 11.9, 4,096 x 256 29.5 / 29.8, 8,192
+// x 64 19.5 / 19.8, 18,432 x 64 80.2 / 80.7; below the line 512 x 64 5.5 / 4.5, 1,024 x
+// 64 6.0 / 5.7, 2,048 x 64 7.6 / 7.4. Long: 3,000 H2O x 128 30.9 / 30.6, x 192 43.6 /
+// 42.9, x 256 53.3 / 52.5, x 512 110 / 109; mixed x 192 39.2 / 38.1, x 256 42.7 / 41.9.
+// Inner CG, 10 iterations, short rows: 18,432 x 190 columns 185 / 191, 18,432 x 64 59.0
+// / 60.6, 4,096 x 64 9.6 / 9.8, 4,096 x 256 22.3 / 23.1.
 inline int product_waves(int64_t nb, int chunks, int64_t row_orbitals) {
     return !long_rows(row_orbitals) && nb * chunks >= 4096 ? 1 : 4;
 }
 
 // Waves that a launch of Chebyshev steps (or of their residuals) gives a block row;
-// narrow: complex64 with one column a lane.  Four, except for short rows in launches
-// of one chunk with enough rows: the waves of one chunk then fill the card without
-// sharing, whose LDS pass and barriers are left as cost.  60 (member of N 76,152:
-// 120) iterations with 64 columns a launch, ms in the steps, four / one: FP64 N
-// 76,152 462 / 455, N 122,196 318 / 314, N 131,072 571 / 556; mixed 290 / 279, 210 /
-// 199, 318 / 292, their FP64 residuals 62 / 60, 43 / 41, 79 / 75.  Below, whole runs
-// of 30 iterations, four / one: FP64 12,288 rows 30.4 / 29.9 ms, 8,192 rows 19.2 /
-// 19.9; mixed 4,096 rows 12.2 / 11.7, 2,048 rows the same.  Two chunks and more, or
-// two columns a lane, mixed: 8,192 rows x 128 columns 27.0 / 29.2.  Long rows, 12,000
-// H2O x 64 columns: FP64 62 / 67, mixed 51 / 55.
+// narrow: complex64 with one column a lane. Four, except for short rows in launches of
+// one chunk with enough rows: the waves of one chunk then fill the card without
+// sharing, whose LDS pass and barriers are left as cost. Runs of 30 iterations with 64
+// columns, ms, four / one: FP64 8,192 rows 19.5 / 20.2, 12,288 30.1 / 29.3, 18,432 83.1
+// / 80.2, 32,768 74.7 / 72.8; mixed 2,048 rows 7.7 / 7.9, 4,096 12.0 / 12.0 (8 columns
+// 10.3 / 10.0), 8,192 19.3 / 19.0, 12,288 26.0 / 25.0, 18,432 70.3 / 66.4, 32,768 63.1
+// / 60.4. Two chunks and more, or two columns a lane, mixed: 8,192 rows x 128 columns
+// 27.0 / 29.2. Long rows (with the seed product), 12,000 H2O x 64 columns: FP64 60.6 /
+// 62.8, mixed 49.0 / 53.7.
 inline int step_waves(int64_t nb, int chunks, int64_t row_orbitals, bool narrow) {
     return !long_rows(row_orbitals) && chunks == 1 && nb >= (narrow ? 4096 : 12288) ? 1 : 4;
 }

@@ -12,9 +12,11 @@
 // between iterations.
 //
 // What bounds it is one CU's product: the chain of LDS reads and fmas of a
-// Chebyshev step (about 1 us at N = 256).  Measured, tiles -> this kernel, 64
-// shifts: Green's functions N 256 R 8 36.6 -> 8.5 ms, charges N 144 R 48
-// 26.8 -> 6.6 ms, gradients N 384 R 64 124 -> 60 ms, N 384 R 384 158 -> 109 ms.
+// Chebyshev step (about 1 us at N = 256).  Measured, the tiled path
+// that it replaced -> this kernel, 64 shifts: Green's functions N 256 R 8 47 -> 8.3
+// ms, charges N 144 R 144 32 -> 4.6 ms, gradients of a loss N 384 R 130 221 -> 60 ms,
+// of the band energy N 384 R 384 255 -> 114 ms (the product of the tiles has become
+// faster since: 37, 27, - and 158 ms there).
 // One row a lane read LDS twice as often; unpacked S and H cost a gather of
 // 8-byte values; more blocks in registers spilled (rows below: the fastest of
 // a scan, in blocks a lane keeps of S and of H).

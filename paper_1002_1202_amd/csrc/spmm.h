@@ -210,7 +210,7 @@ struct NoCombine {
 // Y = factor_c S X - H X, X and Y [N][R] of the caller (not overlapping),
 // factors [R] complex in host memory.  More than kProductFactors columns with
 // factors of their own take one launch and a device copy of the factors in room
-// [R], instead of a launch for each 128 (64 block rows, 1000 columns: 43 against 87 us).
+// [R], instead of a launch for each 128 (64 block rows, 1000 columns: 36 against 87 us).
 constexpr int kProductFactors = 512;
 void launch_product(hipStream_t st, const Pair &pr, int R, const double *factors, const c128 *X, c128 *Y, c128 *room);
 

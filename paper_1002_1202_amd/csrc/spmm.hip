@@ -1,7 +1,8 @@
 // Block-sparse products with H and S for many right-hand sides at once.
 //
 // One workgroup walks one block row for 64 lanes of columns, its four waves a
-// quarter of the stored blocks each (spmm.h); the B x B blocks of S and H are
+// quarter of the stored blocks each, or four rows, one a wave, in launches of many
+// short rows (spmm.h, geometry.h); the B x B blocks of S and H are
 // wave-uniform (scalar loads), the gathered x rows are 64 contiguous values
 // per orbital (one coalesced 1 KiB transaction per orbital row).  No MFMA: per
 // stored value the product does 2 (S only) or 4 (S and H) FMAs per complex
@@ -71,8 +72,8 @@ __global__ __launch_bounds__(kBlock) void k_spmm_seed(
 // The same product for a caller's own X and Y, R columns wide: rows of any
 // length, the lanes beyond the last column masked, and the columns' factors in
 // the kernel's arguments.  Against padded copies of X and Y around the kernel
-// above and factors copied to the device: 64 Si x 8 columns 36.4 -> 24 us a call,
-// 8,192 Si x 250 278 -> 183 us.  Four waves share a row at every size (one wave a
+// above and factors copied to the device: 64 Si x 8 columns 41.7 -> 22.5 us a call,
+// 8,192 Si x 250 307 -> 191 us.  Four waves share a row at every size (one wave a
 // row: 102 against 85 us for 8,192 Si x 128); without the dots there is nothing to
 // load beside the product.
 constexpr int kFactors = 128;
